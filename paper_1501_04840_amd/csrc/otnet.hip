@@ -1,6 +1,8 @@
 // Kernels of the warm-start network: convolutions as implicit GEMMs on the
 // gfx950 matrix cores (BF16 operands, FP32 accumulation) and the pooling,
 // upsampling, loss, optimiser and layout pieces around them.
+#include <algorithm>
+
 #include "net_common.h"
 
 namespace otn {
@@ -197,13 +199,25 @@ __global__ void __launch_bounds__(kThreads) k_wgrad_reduce(const float* part, in
     out[i] = s;
 }
 
-__global__ void __launch_bounds__(kThreads) k_pack_input(const float* x, int in_ch, long long npix,
-                                                        bf16_t* out, int ld) {
-    const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= npix * ld) return;
-    const long long p = i / ld;
-    const int c = (int)(i - p * ld);
-    out[i] = c < in_ch ? f2bf(x[p * in_ch + c]) : (bf16_t)0;
+// BF16 copy of the FP32 input, channels padded to ld (a multiple of 8) with
+// zeros: eight output channels per thread, one 16-byte store.  Bound by HBM
+// (4 bytes read, 2 written per channel): 131072 pixels of 195 channels take
+// 26 us (5.9 TB/s) against 59 us with one channel and one 64-bit division per
+// thread.
+template <typename I>
+__global__ void __launch_bounds__(kThreads) k_pack_input(const float* __restrict__ x, int in_ch,
+                                                        long long npix, bf16_t* __restrict__ out,
+                                                        int ld) {
+    const I l8 = (I)(ld / 8);
+    const I i = (I)blockIdx.x * kThreads + threadIdx.x;
+    if (i >= (I)npix * l8) return;
+    const I p = i / l8;
+    const int c = (int)(i - p * l8) * 8;
+    const float* s = x + (long long)p * in_ch + c;
+    float f[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) f[q] = c + q < in_ch ? s[q] : 0.f;
+    *reinterpret_cast<uint4*>(out + (long long)i * 8) = pack8(f);
 }
 
 // dst[b][y][x][c] = mean of the 2x2 source block (8 channels per thread).
@@ -395,75 +409,187 @@ __global__ void __launch_bounds__(kThreads) k_param_map(const float* src, float*
 
 // ---- solver glue ----------------------------------------------------------
 
-// x[b][y][x] = (f0 channels, f1 channels, then base channels if base is given).
-__global__ void __launch_bounds__(kThreads) k_warm_inputs(WarmGeom g, int nb, const float* f0,
-                                                         const float* f1, const float* base,
-                                                         float* x) {
-    const long long plane = (long long)g.X * g.Y;
-    const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= nb * plane) return;
-    const long long b = i / plane, p = i - b * plane;
+// x[b][y][x] = (f0 channels, f1 channels, then base channels if base is given):
+// four consecutive output floats per thread (one 16-byte store; a group may
+// run over a pixel's end).  A thread per pixel, each lane writing its own row,
+// moved a 64-byte sector per 4-byte store: 262144 pixels of 195 channels took
+// 1590 us; consecutive outputs take 122 us.
+template <typename I>
+__global__ void __launch_bounds__(kThreads) k_warm_inputs(WarmGeom g, int nb,
+                                                         const float* __restrict__ f0,
+                                                         const float* __restrict__ f1,
+                                                         const float* __restrict__ base,
+                                                         float* __restrict__ x) {
+    const I plane = (I)g.X * g.Y;
     const int nch = g.C * (g.P - 1) + 3 * g.C * g.P;
     const int in_ch = 2 * g.C + (base ? nch : 0);
-    float* o = x + i * in_ch;
-    for (int c = 0; c < g.C; ++c) {
-        o[c] = f0[(b * g.C + c) * plane + p];
-        o[g.C + c] = f1[(b * g.C + c) * plane + p];
+    const I n = (I)nb * plane * in_ch;
+    const I e0 = 4 * ((I)blockIdx.x * kThreads + threadIdx.x);
+    if (e0 >= n) return;
+    I i = e0 / in_ch;                                  // pixel (over the batch)
+    int ch = (int)(e0 - i * in_ch);
+    float v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (ch >= 2 * g.C) {
+            v[q] = i < (I)nb * plane ? base[(long long)i * nch + ch - 2 * g.C] : 0.f;
+        } else if (i < (I)nb * plane) {
+            const I b = i / plane, p = i - b * plane;
+            const float* f = ch < g.C ? f0 : f1;
+            v[q] = f[((long long)b * g.C + (ch < g.C ? ch : ch - g.C)) * plane + p];
+        } else {
+            v[q] = 0.f;
+        }
+        if (++ch == in_ch) { ch = 0; ++i; }
     }
-    if (base)
-        for (int q = 0; q < nch; ++q) o[2 * g.C + q] = base[i * nch + q];
+    if (e0 + 4 <= n && ((uintptr_t)x & 15) == 0) {
+        *reinterpret_cast<float4*>(x + e0) = make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (e0 + q < n) x[e0 + q] = v[q];
+    }
 }
 
-// One thread per pixel; mode 0 writes the target (state minus base) from
-// the state, mode 1 the state from a network output (plus base).
+// Between the planar solver state and the channels-last network layout: mode 0
+// writes the target (state minus base) from the state, mode 1 the state from a
+// network output (plus base).  A block maps 64 consecutive pixels (a lane
+// each on the planar side) x 64 channels (a lane each on the channels-last
+// side) through LDS, so both sides move 256-byte runs.  With a thread per
+// pixel walking its channels, each lane of the channels-last side was on a
+// line of its own: 64 problems of 64 x 64 x 3 x 16 took 820 us (mode 0, no
+// base) and 1440 us (mode 1 with base); now 96 and 165 us (4.1 and 3.6 TB/s of 4-byte lanes).
+constexpr int kMapPix = 64, kMapCh = 64, kMapPitch = kMapCh + 1;
+
+// One channel of the network layout in the planar state: q < 0 a density
+// slice with its interpolation weight s, else the momentum component q; off
+// the offset k slice + c plane of its time step and colour.
+struct MapChan {
+    long long off;
+    int q, c;
+    float s;
+};
+
 template <int MODE>
-__global__ void __launch_bounds__(kThreads) k_warm_map(WarmGeom g, int nb, const float* f0,
-                                                      const float* f1, const float* Fr, float* Fw,
+__global__ void __launch_bounds__(kThreads) k_warm_map(WarmGeom g, int nb,
+                                                      const float* __restrict__ f0,
+                                                      const float* __restrict__ f1, const float* Fr, float* Fw,
                                                       long long sF, const float* Mxr,
                                                       const float* Myr, const float* Mcr,
                                                       float* Mxw, float* Myw, float* Mcw,
                                                       long long sM, const float* yr,
                                                       const float* base, float* tw) {
+    __shared__ float tb[kMapPix * kMapPitch];                        // base, then (mode 0) the target
+    __shared__ float ty[MODE == 1 ? kMapPix * kMapPitch : 1];        // network output
+    // the tile's channels, decoded once: their divisions in every wave and
+    // channel were half of the instructions
+    __shared__ MapChan chan[kMapCh];
     const long long plane = (long long)g.X * g.Y;
-    const long long slice = plane * g.C;
-    const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= nb * plane) return;
-    const long long b = i / plane, p = i - b * plane;
-    const int x = (int)(p % g.X), y = (int)(p / g.X);
+    const long long slice = plane * g.C, npix = nb * plane;
     const int P = g.P, C = g.C;
-    const int nch = C * (P - 1) + 3 * C * P;
-    const long long tb = i * nch;
-    for (int k = 1; k < P; ++k) {
-        const float s = (float)k / (float)P;
-        for (int c = 0; c < C; ++c) {
-            const long long e = (b * C + c) * plane + p;
-            const float lin = (1.f - s) * f0[e] + s * f1[e];
-            const long long fi = b * sF + k * slice + (long long)c * plane + p;
-            const long long ti = tb + (k - 1) * C + c;
-            const float bs = base ? base[ti] : 0.f;
-            if (MODE == 0)
-                tw[ti] = Fr[fi] - lin - bs;
-            else
-                Fw[fi] = lin + yr[ti] + bs;
+    const int o0 = C * (P - 1), nch = o0 + 3 * C * P;
+    const int cl = threadIdx.x % kMapCh, pl = threadIdx.x % kMapPix;      // channel, pixel of a thread
+    const int cr = threadIdx.x / kMapCh, pr = __builtin_amdgcn_readfirstlane(threadIdx.x / kMapPix);
+    constexpr int CR = kThreads / kMapCh, PR = kThreads / kMapPix;        // pixels, channels per round
+    const long long i0 = (long long)blockIdx.x * kMapPix;
+    const int np = (int)min((long long)kMapPix, npix - i0);
+    // the channel tiles in turn (their runs of a pixel's row share cache lines;
+    // as blocks of their own, on other XCDs, they fetched those lines twice)
+    for (int ch0 = 0; ch0 < nch; ch0 += kMapCh) {
+        const int nc = min(kMapCh, nch - ch0);
+        if (ch0) __syncthreads();
+        if ((int)threadIdx.x < nc) {
+            const int ch = ch0 + threadIdx.x;
+            MapChan h;
+            int k;
+            if (ch < o0) {
+                k = 1 + ch / C;
+                h.q = -1;
+                h.c = ch % C;
+            } else {
+                const int kc = (ch - o0) % (P * C);
+                k = kc / C;
+                h.q = (ch - o0) / (P * C);
+                h.c = kc % C;
+            }
+            h.s = (float)k / (float)P;
+            h.off = k * slice + (long long)h.c * plane;
+            chan[threadIdx.x] = h;
         }
-    }
-    const long long o0 = (long long)C * (P - 1);
-    for (int q = 0; q < 3; ++q) {
-        const bool wallrow = (q == 0 && !g.perx && x == 0) || (q == 1 && !g.pery && y == 0);
-        for (int k = 0; k < P; ++k)
-            for (int c = 0; c < C; ++c) {
-                const bool wall = wallrow || (q == 2 && !g.perc && c == 0);
-                const long long mi = b * sM + k * slice + (long long)c * plane + p;
-                const long long ti = tb + o0 + ((long long)q * P + k) * C + c;
-                const float bs = base ? base[ti] : 0.f;
-                if (MODE == 0) {
-                    const float* M = q == 0 ? Mxr : (q == 1 ? Myr : Mcr);
-                    tw[ti] = wall ? 0.f : M[mi] - bs;
-                } else {
-                    float* M = q == 0 ? Mxw : (q == 1 ? Myw : Mcw);
-                    M[mi] = wall ? 0.f : yr[ti] + bs;
+        // channels-last side: a lane per channel; every load in flight (outside
+        // the tile: its first entry) before the first LDS store
+        {
+            constexpr int R = kMapPix / CR;
+            float vb[R], vy[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int q = cr + j * CR;
+                const long long e = i0 * nch + (q < np && cl < nc ? q * nch + ch0 + cl : 0);
+                vb[j] = base ? base[e] : 0.f;
+                vy[j] = MODE == 1 ? yr[e] : 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int l = (cr + j * CR) * kMapPitch + cl;
+                tb[l] = vb[j];
+                if (MODE == 1) ty[l] = vy[j];
+            }
+        }
+        __syncthreads();
+        // planar side: a lane per pixel
+        const long long i = i0 + pl;
+        if (pl < np) {
+            const long long b = i / plane, p = i - b * plane;
+            const int x = (int)(p % g.X), y = (int)(p / g.X);
+            const bool wx = !g.perx && x == 0, wy = !g.pery && y == 0;
+            const long long bF = b * sF + p, bM = b * sM + p, bf = b * slice + p;
+            constexpr int R = kMapCh / PR, Q = 8;
+            const bool dens = ch0 < o0;                      // the tile has density channels
+#pragma unroll 1
+            for (int j0 = 0; j0 < R; j0 += Q) {
+                // the state (mode 0) and the end densities of Q channels in flight
+                // (past the tile: its first channel)
+                float v[Q], a0[Q], a1[Q];
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    const int cc = pr + (j0 + j) * PR;
+                    const MapChan h = chan[cc < nc ? cc : 0];
+                    if (MODE == 0)
+                        v[j] = h.q < 0 ? Fr[bF + h.off] : (h.q == 0 ? Mxr : h.q == 1 ? Myr : Mcr)[bM + h.off];
+                    a0[j] = dens ? f0[bf + h.c * plane] : 0.f;
+                    a1[j] = dens ? f1[bf + h.c * plane] : 0.f;
+                }
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    const int cc = pr + (j0 + j) * PR, l = pl * kMapPitch + cc;
+                    if (cc >= nc) break;
+                    const MapChan h = chan[cc];
+                    const float bs = tb[l];
+                    if (h.q < 0) {
+                        // (1 - s) f0 + s f1, the second product rounded
+                        const float lin = fmaf(1.f - h.s, a0[j], h.s * a1[j]);
+                        if (MODE == 0)
+                            tb[l] = v[j] - lin - bs;
+                        else
+                            Fw[bF + h.off] = lin + ty[l] + bs;
+                    } else {
+                        const bool wall = (h.q == 0 && wx) || (h.q == 1 && wy) ||
+                                          (h.q == 2 && !g.perc && h.c == 0);
+                        if (MODE == 0)
+                            tb[l] = wall ? 0.f : v[j] - bs;
+                        else
+                            (h.q == 0 ? Mxw : h.q == 1 ? Myw : Mcw)[bM + h.off] = wall ? 0.f : ty[l] + bs;
+                    }
                 }
             }
+        }
+        if (MODE == 0) {
+            __syncthreads();
+            if (cl < nc)
+#pragma unroll 4
+                for (int q = cr; q < np; q += CR)
+                    tw[(i0 + q) * nch + ch0 + cl] = tb[q * kMapPitch + cl];
+        }
     }
 }
 
@@ -505,7 +631,10 @@ __device__ inline Lerp lerp_at(float u, int n, int periodic) {
 // Prolong a coarse state (X/2, Y/2, same C, P_c steps) to the fine grid:
 // bilinear in space for cell-centred values, linear between faces for the
 // staggered momenta (walls read as 0), linear in time.  Writes the unknown
-// slices of F and every slot of Mx, My, Mc.
+// slices of F and every slot of Mx, My, Mc.  A block per 256 pixels and time
+// step (blockIdx.y): a thread walking every step of its pixel left the chip
+// waiting on its chain of loads (170 us for 64 problems of 64 x 64 x 3 x 16;
+// now 155 us).
 __global__ void __launch_bounds__(kThreads) k_prolong(WarmGeom gc, WarmGeom gf, int nb,
                                                      const float* Fc, long long sFc,
                                                      const float* Mxc, const float* Myc,
@@ -534,52 +663,58 @@ __global__ void __launch_bounds__(kThreads) k_prolong(WarmGeom gc, WarmGeom gf, 
         if (periodic) return row[(long long)(((j % n) + n) % n) * stride];
         return (j <= 0 || j >= n) ? 0.f : row[(long long)j * stride];
     };
-    for (int k = 1; k < gf.P; ++k) {
-        float s = k * rt;
-        int j0 = min((int)floorf(s), gc.P - 1);
-        const float a = s - (float)j0;
-        for (int c = 0; c < gf.C; ++c) {
-            const long long o0 = b * sFc + j0 * slc + (long long)c * pc;
-            const float v = (1.f - a) * centred(Fc, o0) + a * centred(Fc, o0 + slc);
-            F[b * sF + k * slf + (long long)c * plane + p] = v;
-        }
-    }
-    for (int k = 0; k < gf.P; ++k) {
-        const Lerp ct = lerp_at((k + 0.5f) * rt - 0.5f, gc.P, 0);
-        for (int c = 0; c < gf.C; ++c) {
-            const long long mi = b * sM + k * slf + (long long)c * plane + p;
-            float vt[3] = {0.f, 0.f, 0.f};
-            for (int h = 0; h < 2; ++h) {
-                const int kc = h ? ct.b : ct.a;
-                const float wt = h ? ct.w : 1.f - ct.w;
-                const long long oc = b * sMc + kc * slc + (long long)c * pc;
-                // x faces: fine slot x sits at coarse face position x / 2
-                {
-                    const int j0 = x >> 1;
-                    const float w = (x & 1) ? 0.5f : 0.f;
-                    const float* r0 = Mxc + oc + (long long)cy.a * gc.X;
-                    const float* r1 = Mxc + oc + (long long)cy.b * gc.X;
-                    const float v0 = (1.f - w) * face(r0, j0, gc.X, 1, gf.perx) + w * face(r0, j0 + 1, gc.X, 1, gf.perx);
-                    const float v1 = (1.f - w) * face(r1, j0, gc.X, 1, gf.perx) + w * face(r1, j0 + 1, gc.X, 1, gf.perx);
-                    vt[0] += wt * ((1.f - cy.w) * v0 + cy.w * v1);
-                }
-                {
-                    const int j0 = y >> 1;
-                    const float w = (y & 1) ? 0.5f : 0.f;
-                    const float* c0 = Myc + oc + cx.a;
-                    const float* c1 = Myc + oc + cx.b;
-                    const float v0 = (1.f - w) * face(c0, j0, gc.Y, gc.X, gf.pery) + w * face(c0, j0 + 1, gc.Y, gc.X, gf.pery);
-                    const float v1 = (1.f - w) * face(c1, j0, gc.Y, gc.X, gf.pery) + w * face(c1, j0 + 1, gc.Y, gc.X, gf.pery);
-                    vt[1] += wt * ((1.f - cx.w) * v0 + cx.w * v1);
-                }
-                vt[2] += wt * centred(Mcc, oc);
+    for (int k = blockIdx.y; k < gf.P; k += gridDim.y) {
+        if (k > 0) {
+            float s = k * rt;
+            int j0 = min((int)floorf(s), gc.P - 1);
+            const float a = s - (float)j0;
+            for (int c = 0; c < gf.C; ++c) {
+                const long long o0 = b * sFc + j0 * slc + (long long)c * pc;
+                const float v = (1.f - a) * centred(Fc, o0) + a * centred(Fc, o0 + slc);
+                F[b * sF + k * slf + (long long)c * plane + p] = v;
             }
-            const bool wx = !gf.perx && x == 0, wy = !gf.pery && y == 0, wc = !gf.perc && c == 0;
-            Mx[mi] = wx ? 0.f : vt[0];
-            My[mi] = wy ? 0.f : vt[1];
-            Mc[mi] = wc ? 0.f : vt[2];
+        }
+        {
+            const Lerp ct = lerp_at((k + 0.5f) * rt - 0.5f, gc.P, 0);
+            for (int c = 0; c < gf.C; ++c) {
+                const long long mi = b * sM + k * slf + (long long)c * plane + p;
+                float vt[3] = {0.f, 0.f, 0.f};
+                for (int h = 0; h < 2; ++h) {
+                    const int kc = h ? ct.b : ct.a;
+                    const float wt = h ? ct.w : 1.f - ct.w;
+                    const long long oc = b * sMc + kc * slc + (long long)c * pc;
+                    // x faces: fine slot x sits at coarse face position x / 2
+                    {
+                        const int j0 = x >> 1;
+                        const float w = (x & 1) ? 0.5f : 0.f;
+                        const float* r0 = Mxc + oc + (long long)cy.a * gc.X;
+                        const float* r1 = Mxc + oc + (long long)cy.b * gc.X;
+                        const float v0 = (1.f - w) * face(r0, j0, gc.X, 1, gf.perx) + w * face(r0, j0 + 1, gc.X, 1, gf.perx);
+                        const float v1 = (1.f - w) * face(r1, j0, gc.X, 1, gf.perx) + w * face(r1, j0 + 1, gc.X, 1, gf.perx);
+                        vt[0] += wt * ((1.f - cy.w) * v0 + cy.w * v1);
+                    }
+                    {
+                        const int j0 = y >> 1;
+                        const float w = (y & 1) ? 0.5f : 0.f;
+                        const float* c0 = Myc + oc + cx.a;
+                        const float* c1 = Myc + oc + cx.b;
+                        const float v0 = (1.f - w) * face(c0, j0, gc.Y, gc.X, gf.pery) + w * face(c0, j0 + 1, gc.Y, gc.X, gf.pery);
+                        const float v1 = (1.f - w) * face(c1, j0, gc.Y, gc.X, gf.pery) + w * face(c1, j0 + 1, gc.Y, gc.X, gf.pery);
+                        vt[1] += wt * ((1.f - cx.w) * v0 + cx.w * v1);
+                    }
+                    vt[2] += wt * centred(Mcc, oc);
+                }
+                const bool wx = !gf.perx && x == 0, wy = !gf.pery && y == 0, wc = !gf.perc && c == 0;
+                Mx[mi] = wx ? 0.f : vt[0];
+                My[mi] = wy ? 0.f : vt[1];
+                Mc[mi] = wc ? 0.f : vt[2];
+            }
         }
     }
+}
+
+dim3 map_grid(const WarmGeom& g, int nb) {
+    return dim3((unsigned)(((long long)nb * g.X * g.Y + kMapPix - 1) / kMapPix));
 }
 
 inline unsigned blocks(long long n) { return (unsigned)((n + kThreads - 1) / kThreads); }
@@ -604,8 +739,14 @@ void launch_wgrad_reduce(const float* part, int splits, int M, int N, float* out
 
 void launch_pack_input(const float* x, int in_ch, long long npix, bf16_t* out, int ld,
                        hipStream_t st) {
-    hipLaunchKernelGGL(k_pack_input, dim3(blocks(npix * ld)), dim3(kThreads), 0, st, x, in_ch, npix,
-                       out, ld);
+    // 32-bit indices (one cheap division) where every one fits
+    const long long n = npix * (ld / 8);
+    if (n < (1LL << 31))
+        hipLaunchKernelGGL(k_pack_input<unsigned>, dim3(blocks(n)), dim3(kThreads), 0, st, x, in_ch,
+                           npix, out, ld);
+    else
+        hipLaunchKernelGGL(k_pack_input<long long>, dim3(blocks(n)), dim3(kThreads), 0, st, x, in_ch,
+                           npix, out, ld);
 }
 
 void launch_pool(View src, int C, int nb, int H, int W, bf16_t* dst, hipStream_t st) {
@@ -664,16 +805,20 @@ void launch_param_map(const float* src, float* dst, int taps, int cin_o, int cou
 
 void launch_warm_inputs(const WarmGeom& g, int nb, const float* f0, const float* f1,
                         const float* base, float* x, hipStream_t st) {
-    const long long n = (long long)nb * g.X * g.Y;
-    hipLaunchKernelGGL(k_warm_inputs, dim3(blocks(n)), dim3(kThreads), 0, st, g, nb, f0, f1, base, x);
+    const int in_ch = 2 * g.C + (base ? g.C * (g.P - 1) + 3 * g.C * g.P : 0);
+    const long long n = (long long)nb * g.X * g.Y * in_ch;
+    const dim3 grid(blocks((n + 3) / 4));
+    if (n < (1LL << 31) - 4 * kThreads)
+        hipLaunchKernelGGL(k_warm_inputs<unsigned>, grid, dim3(kThreads), 0, st, g, nb, f0, f1, base, x);
+    else
+        hipLaunchKernelGGL(k_warm_inputs<long long>, grid, dim3(kThreads), 0, st, g, nb, f0, f1, base, x);
 }
 
 void launch_warm_targets(const WarmGeom& g, int nb, const float* f0, const float* f1,
                          const float* F, long long sF, const float* Mx, const float* My,
                          const float* Mc, long long sM, const float* base, float* t,
                          hipStream_t st) {
-    const long long n = (long long)nb * g.X * g.Y;
-    hipLaunchKernelGGL(k_warm_map<0>, dim3(blocks(n)), dim3(kThreads), 0, st, g, nb, f0, f1, F,
+    hipLaunchKernelGGL(k_warm_map<0>, map_grid(g, nb), dim3(kThreads), 0, st, g, nb, f0, f1, F,
                        (float*)nullptr, sF, Mx, My, Mc, (float*)nullptr, (float*)nullptr,
                        (float*)nullptr, sM, (const float*)nullptr, base, t);
 }
@@ -681,8 +826,7 @@ void launch_warm_targets(const WarmGeom& g, int nb, const float* f0, const float
 void launch_warm_state(const WarmGeom& g, int nb, const float* f0, const float* f1,
                        const float* y, const float* base, float* F, long long sF, float* Mx,
                        float* My, float* Mc, long long sM, hipStream_t st) {
-    const long long n = (long long)nb * g.X * g.Y;
-    hipLaunchKernelGGL(k_warm_map<1>, dim3(blocks(n)), dim3(kThreads), 0, st, g, nb, f0, f1,
+    hipLaunchKernelGGL(k_warm_map<1>, map_grid(g, nb), dim3(kThreads), 0, st, g, nb, f0, f1,
                        (const float*)nullptr, F, sF, (const float*)nullptr, (const float*)nullptr,
                        (const float*)nullptr, Mx, My, Mc, sM, y, base, (float*)nullptr);
 }
@@ -697,7 +841,7 @@ void launch_prolong(const WarmGeom& gc, const WarmGeom& gf, int nb, const float*
                     long long sMc, float* F, long long sF, float* Mx, float* My, float* Mc,
                     long long sM, hipStream_t st) {
     const long long n = (long long)nb * gf.X * gf.Y;
-    hipLaunchKernelGGL(k_prolong, dim3(blocks(n)), dim3(kThreads), 0, st, gc, gf, nb, Fc, sFc, Mxc,
+    hipLaunchKernelGGL(k_prolong, dim3(blocks(n), (unsigned)std::min(gf.P, 65535)), dim3(kThreads), 0, st, gc, gf, nb, Fc, sFc, Mxc,
                        Myc, Mcc, sMc, F, sF, Mx, My, Mc, sM);
 }
 
