@@ -25,9 +25,11 @@ struct Layer {
     int taps, cin_o, cout_o, cin_p, cout_p;
     long long off_o;      // offset in the exchanged flat vector
     long long off_p;      // offset in the padded device vector (weights, then biases)
-    long long off_w;      // offset of this layer's BF16 copies
+    long long off_wf, off_wb;   // offsets of this layer's BF16 copies (fragment order)
     long long np() const { return (long long)taps * cin_p * cout_p + cout_p; }
     long long nw() const { return (long long)taps * cin_p * cout_p; }
+    long long nwf() const { return frag_elems(cout_p, taps * cin_p); }
+    long long nwb() const { return frag_elems(cin_p, taps * cout_p); }
 };
 
 // Layer list in execution order: encoder (2 per level), decoder (2 per level
@@ -57,14 +59,16 @@ std::vector<Layer> make_layers(const ot_net_desc& d) {
         c = w;
     }
     add(1, c, d.out_ch);
-    long long oo = 0, op = 0, ow = 0;
+    long long oo = 0, op = 0, of = 0, ob = 0;
     for (auto& l : L) {
         l.off_o = oo;
         l.off_p = op;
-        l.off_w = ow;
+        l.off_wf = of;
+        l.off_wb = ob;
         oo += (long long)l.taps * l.cin_o * l.cout_o + l.cout_o;
         op += l.np();
-        ow += l.nw();
+        of += l.nwf();
+        ob += l.nwb();
     }
     return L;
 }
@@ -102,7 +106,7 @@ struct ot_net {
     ot_net_desc d;
     hipStream_t st;
     std::vector<Layer> layers;
-    long long np_o = 0, np_p = 0, nw = 0;
+    long long np_o = 0, np_p = 0;
     // parameters and optimiser
     float *master = nullptr, *mom1 = nullptr, *mom2 = nullptr, *grad = nullptr;
     bf16_t *wf = nullptr, *wb = nullptr;
@@ -129,10 +133,11 @@ namespace {
 // Workspace layout; with n == nullptr only the size is computed.
 size_t carve(const ot_net_desc& d, ot_net* n, char* base) {
     const auto layers = make_layers(d);
-    long long np = 0, nw = 0;
+    long long np = 0, nwf = 0, nwb = 0;
     for (auto& l : layers) {
         np += l.np();
-        nw += l.nw();
+        nwf += l.nwf();
+        nwb += l.nwb();
     }
     size_t o = 0;
     auto take = [&](size_t bytes) -> char* {
@@ -146,8 +151,8 @@ size_t carve(const ot_net_desc& d, ot_net* n, char* base) {
     float* m1 = (float*)take(np * 4);
     float* m2 = (float*)take(np * 4);
     float* gr = (float*)take(np * 4);
-    bf16_t* wf = (bf16_t*)take(nw * 2);
-    bf16_t* wb = (bf16_t*)take(nw * 2);
+    bf16_t* wf = (bf16_t*)take((nwf + kConvPad) * 2);
+    bf16_t* wb = (bf16_t*)take((nwb + kConvPad) * 2);
     std::vector<bf16_t*> a(L), cat(L), pool(L), da(L), db(L), gcat(L), gz1(L), gz2(L), gpool(L);
     bf16_t* bot = nullptr;
     const int cin0 = pad8(d.in_ch), coutp = pad8(d.out_ch);
@@ -194,7 +199,6 @@ size_t carve(const ot_net_desc& d, ot_net* n, char* base) {
     if (n) {
         n->layers = layers;
         n->np_p = np;
-        n->nw = nw;
         n->master = master;
         n->mom1 = m1;
         n->mom2 = m2;
@@ -244,7 +248,7 @@ void conv_fwd(ot_net* n, int li, int nb, int lev, View src, void* dst, int dst_l
     a.src_ld = src.ld;
     a.cin = l.cin_p;
     a.taps = l.taps;
-    a.wmat = n->wf + l.off_w;
+    a.wmat = n->wf + l.off_wf;
     a.nb = nb;
     a.H = n->d.H >> lev;
     a.W = n->d.W >> lev;
@@ -256,7 +260,7 @@ void conv_fwd(ot_net* n, int li, int nb, int lev, View src, void* dst, int dst_l
     a.dst_off = dst_off;
     a.dst_n = dst_n;
     a.bias = bias_of(n, l);
-    launch_conv(a, MODE_CONV, epi, 1, n->st);
+    launch_conv(a, epi, n->st);
 }
 
 // Input gradient: dst = conv^T(dz), masked by mask > 0 when mask is given.
@@ -268,7 +272,7 @@ void conv_bwd_data(ot_net* n, int li, int nb, int lev, const bf16_t* dz, bf16_t*
     a.src_ld = l.cout_p;
     a.cin = l.cout_p;
     a.taps = l.taps;
-    a.wmat = n->wb + l.off_w;
+    a.wmat = n->wb + l.off_wb;
     a.nb = nb;
     a.H = n->d.H >> lev;
     a.W = n->d.W >> lev;
@@ -281,7 +285,7 @@ void conv_bwd_data(ot_net* n, int li, int nb, int lev, const bf16_t* dz, bf16_t*
     a.dst_n = l.cin_p;
     a.mask = mask;
     a.mask_ld = mask_ld;
-    launch_conv(a, MODE_CONV, mask ? EPI_MASK : EPI_PLAIN, 1, n->st);
+    launch_conv(a, mask ? EPI_MASK : EPI_PLAIN, n->st);
 }
 
 // Weight and bias gradient of layer li into n->grad.
@@ -309,7 +313,7 @@ int conv_wgrad(ot_net* n, int li, int nb, int lev, View src, const bf16_t* dz) {
     a.dst = n->part;
     a.dst_ld = a.N;
     a.dst_n = a.N;
-    launch_conv(a, MODE_WGRAD, EPI_PART, s.splits, n->st);
+    launch_wgrad(a, s.splits, n->st);
     launch_wgrad_reduce(n->part, s.splits, a.M, a.N, n->grad + l.off_p, n->st);
     return OT_OK;
 }
@@ -387,8 +391,8 @@ int backward(ot_net* n, int nb) {
 
 void export_weights(ot_net* n) {
     for (auto& l : n->layers)
-        launch_export(n->master + l.off_p, l.taps, l.cin_p, l.cout_p, n->wf + l.off_w,
-                      n->wb + l.off_w, n->st);
+        launch_export(n->master + l.off_p, l.taps, l.cin_p, l.cout_p, n->wf + l.off_wf,
+                      n->wb + l.off_wb, n->st);
 }
 
 int loss_and_grad(ot_net* n, int nb, const float* x, const float* t, const float* cw, double* loss) {

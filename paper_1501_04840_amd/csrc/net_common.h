@@ -8,25 +8,30 @@ namespace otn {
 
 typedef uint16_t bf16_t;   // BF16 storage (upper half of an IEEE float)
 
-enum { MODE_CONV = 0, MODE_WGRAD = 1 };
-enum { EPI_RELU = 0, EPI_F32 = 1, EPI_PLAIN = 2, EPI_MASK = 3, EPI_PART = 4 };
+enum { EPI_RELU = 0, EPI_F32 = 1, EPI_PLAIN = 2, EPI_MASK = 3 };
+
+// BF16 entries of an N x K weight matrix in fragment order (32 outputs x 16 K
+// entries per fragment, both padded).
+__host__ __device__ inline long long frag_elems(int N, int K) {
+    return (long long)((N + 31) / 32) * ((K + 15) / 16) * 512;
+}
 
 // One implicit GEMM of a convolution layer.
-//   MODE_CONV:  out[p][n] = sum_k A[p][k] W[n][k],  A[p][(tap, c)] = src at
-//               pixel p shifted by tap, channel c (0 outside the image);
-//               forward (W = weights) and input gradient (W = flipped
-//               transposed weights, src = output gradient) alike.
-//   MODE_WGRAD: part[z][i][n] = sum over pixels q in split z of
-//               A[i][q] dz[q][n], A[(tap, c)][q] = src at q shifted by tap,
-//               plus a row of ones (i = taps * cin) that yields the bias
-//               gradient.
+//   launch_conv:  out[p][n] = sum_k A[p][k] W[n][k],  A[p][(tap, c)] = src at
+//                 pixel p shifted by tap, channel c (0 outside the image);
+//                 forward (W = weights) and input gradient (W = flipped
+//                 transposed weights, src = output gradient) alike.
+//   launch_wgrad: part[z][i][n] = sum over pixels q in split z of
+//                 A[i][q] dz[q][n], A[(tap, c)][q] = src at q shifted by tap,
+//                 plus a row of ones (i = taps * cin) that yields the bias
+//                 gradient.
 struct ConvArgs {
     const bf16_t* src;
     int src_ld;            // pixel stride of src (elements)
     int cin;               // gathered channels (multiple of 8)
     int taps;              // 9 or 1
-    const bf16_t* wmat;    // MODE_CONV: [N][K] with K = taps * cin
-    const bf16_t* dz;      // MODE_WGRAD: [pixels][dz_ld]
+    const bf16_t* wmat;    // launch_conv: N x K weights in fragment order, K = taps * cin
+    const bf16_t* dz;      // launch_wgrad: [pixels][dz_ld]
     int dz_ld;
     int nb, H, W;
     int M, N, K;
@@ -35,8 +40,12 @@ struct ConvArgs {
     const float* bias;
     const bf16_t* mask;    // EPI_MASK: [pixels][mask_ld]
     int mask_ld;
-    int ksplit;            // MODE_WGRAD: pixels per split
+    int ksplit;            // launch_wgrad: pixels per split
 };
+
+// BF16 entries behind the last fragment of a weight buffer that the
+// convolutions' weight loads, running ahead, may read.
+constexpr int kConvPad = 16 * 512;
 
 // A channels-last view: element (pixel p, channel c) at ptr[p * ld + c].
 struct View {
@@ -44,7 +53,8 @@ struct View {
     int ld;
 };
 
-void launch_conv(const ConvArgs& a, int mode, int epi, int splits, hipStream_t st);
+void launch_conv(const ConvArgs& a, int epi, hipStream_t st);
+void launch_wgrad(const ConvArgs& a, int splits, hipStream_t st);
 void launch_wgrad_reduce(const float* part, int splits, int M, int N, float* out, hipStream_t st);
 void launch_pack_input(const float* x, int in_ch, long long npix, bf16_t* out, int ld,
                        hipStream_t st);

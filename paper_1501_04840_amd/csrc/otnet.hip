@@ -37,22 +37,355 @@ __device__ inline uint4 pack8(const float* f) {
     return v;
 }
 
-// Eight consecutive K entries (one tap, channels c..c+7) of row `pix` of the
-// gathered operand; zero outside the image or past k_end.
-__device__ inline uint4 conv_gather(const ConvArgs& a, int pix, int k, int k_end) {
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (pix >= a.M || k >= k_end) return v;
-    const int tap = k / a.cin, c = k - tap * a.cin;
-    const int hw = a.H * a.W;
-    const int b = pix / hw, r = pix - b * hw;
-    int y = r / a.W, x = r - (r / a.W) * a.W;
-    if (a.taps == 9) {
-        y += tap / 3 - 1;
-        x += tap % 3 - 1;
-        if (y < 0 || y >= a.H || x < 0 || x >= a.W) return v;
-    }
-    return *reinterpret_cast<const uint4*>(a.src + ((long long)(b * a.H + y) * a.W + x) * a.src_ld + c);
+// ---- convolutions and input gradients --------------------------------------
+//
+// out[p][n] = sum_k A[p][k] W[n][k], k = (tap, c).  A block owns 64 pixels (TI
+// images x TH rows x TW columns, or 64 consecutive pixels of a 1x1 layer) and
+// 32 WN outputs.  Its pixels with the one-pixel border, all channels, are
+// staged in LDS once and serve every tap, so the K loop has no barrier: a wave
+// reads its pixel fragments from LDS and its weights, stored in fragment order
+// (one contiguous KB per fragment and 16 K entries), straight from L2, AHEAD
+// steps ahead.  With 64 x 64 block tiles that gathered both operands into LDS
+// for every 32 K entries, the address divisions and the two barriers per stage
+// held the 64 x 64 network's forward pass of 32 images to 108 TFLOP/s (548 us
+// in 15 launches); this form takes 270 us (219 TFLOP/s): 48 us (315 TFLOP/s)
+// for the widest layer, 7-20 us for the others, where few fragments are left
+// per compute unit and a wave's serial K loop and the launch count, 39 us for
+// the FP32 head, bound by its 99 MB.  The sum over k runs in the same steps of
+// 16 in the same order, so results are the same bit for bit.
+//
+// Lane l of a wave holds K entries 8 (l / 32) + 0..7 of row l mod 32 of each
+// operand; accumulator entry r of lane l is row 8 (r / 4) + 4 (l / 32) + r mod
+// 4, column l mod 32.  BF16 outputs take the weights as rows and the pixels as
+// columns (a lane then owns 16 outputs of one pixel, stored as 16-byte
+// pieces); the FP32 head takes the pixels as rows (its unaligned rows are
+// stored one float per lane, 32 consecutive outputs together).
+//
+// LDS layout: 16-byte units of eight channels; a pixel is `pu` units (odd, so
+// that eight neighbours fall in distinct bank groups), a row of the staged tile
+// `ru` units (8 mod 16: the next row takes the other eight groups).
+// Weight fragments in flight: 16 (at 8 the weights' latency still showed:
+// their first reader fetches them from beyond its L2), 4 for fewer steps.
+constexpr int kConvAhead = kConvPad / 512;
+constexpr size_t kConvLds = 156 * 1024;             // staged tiles up to this size
+
+struct ConvGeom {
+    int th_log, tw_log;        // tile rows and columns (3x3 layers)
+    int bw, bh;                // staged columns and rows of one image
+    int ntx, nty;              // tiles along x and y
+    int nc8;                   // units of 8 channels per pixel
+    int pu, ru, iu;            // LDS units per pixel, row, image
+    unsigned mc, mw, mh;       // reciprocals of nc8, bw and bh (e / d = mulhi(e, m), e < 2^16)
+    int entries;               // units to stage
+};
+
+// Steps of the offset table: whole groups and one more.
+__host__ __device__ inline int conv_table(int nsteps, int ahead) {
+    return (nsteps + ahead - 1) / ahead * ahead + ahead;
 }
+
+template <int PF, int WP, int WN, int AHEAD, bool STAGED, int EPI>
+__global__ void __launch_bounds__(64 * WP * WN) k_conv(ConvArgs a, ConvGeom g) {
+    static_assert(PF * WP == 2, "64 pixels per block");
+    constexpr bool SWAP = EPI != EPI_F32;
+    extern __shared__ __attribute__((aligned(16))) uint4 tile[];
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wp = wave % WP, wn = wave / WP;
+    constexpr int NT = 64 * WP * WN;
+    // tile origin: image b0 and (y0, x0), or the linear pixel m0 of a 1x1 layer
+    const int tl = blockIdx.x;
+    const bool one = a.taps == 1;
+    int b0 = 0, y0 = 0, x0 = 0;
+    const int ti = 64 >> (g.th_log + g.tw_log);
+    if (!one) {
+        const int per = g.ntx * g.nty, bi = tl / per, r = tl - bi * per;
+        b0 = bi * ti;
+        y0 = (r / g.ntx) << g.th_log;
+        x0 = (r % g.ntx) << g.tw_log;
+    }
+    if (STAGED) {
+        // Every unit of the tile and its border, zeros outside the image.  The
+        // loads are unconditional (outside: the tensor's first unit), eight in
+        // flight per thread: a load under a condition was waited for before the
+        // next one, which was most of the kernel's time.
+        constexpr int Q = 8;
+        for (int e0 = threadIdx.x; e0 < g.entries; e0 += Q * NT) {
+            uint4 v[Q];
+            int at[Q];
+            bool in[Q];
+#pragma unroll
+            for (int j = 0; j < Q; ++j) {
+                const int e = e0 + j * NT;
+                const int px = g.nc8 == 1 ? e : (int)__umulhi(e, g.mc), u = e - px * g.nc8;
+                long long q;
+                if (one) {
+                    q = 64ll * tl + px;
+                    in[j] = e < g.entries && q < a.M;
+                    at[j] = (px >> 3) * g.ru + (px & 7) * g.pu + u;
+                } else {
+                    const int row = __umulhi(px, g.mw), hx = px - row * g.bw;
+                    const int im = __umulhi(row, g.mh), hy = row - im * g.bh;
+                    const int b = b0 + im, y = y0 + hy - 1, x = x0 + hx - 1;
+                    in[j] = e < g.entries && b < a.nb && (unsigned)y < (unsigned)a.H &&
+                            (unsigned)x < (unsigned)a.W;
+                    q = (long long)(b * a.H + y) * a.W + x;
+                    at[j] = im * g.iu + hy * g.ru + hx * g.pu + u;
+                }
+                v[j] = *reinterpret_cast<const uint4*>(a.src + (in[j] ? q * a.src_ld + 8 * u : 0));
+            }
+#pragma unroll
+            for (int j = 0; j < Q; ++j)
+                if (e0 + j * NT < g.entries) tile[at[j]] = in[j] ? v[j] : make_uint4(0, 0, 0, 0);
+        }
+    }
+    // Where each step's K entries lie, relative to a pixel's first unit: the
+    // byte offset in the tile (or the unit and tap of an unstaged source) of
+    // unit k8 = 2 s + half at steps[half][s], for nsteps rounded up to whole
+    // groups and one group more (those read the pixel's own first unit).  The
+    // K loop reads a group's offsets with a few 16-byte LDS loads instead of
+    // walking taps and channels.
+    const int nk8 = a.K >> 3, nsteps = (nk8 + 1) >> 1, tab = conv_table(nsteps, AHEAD);
+    int* const steps = reinterpret_cast<int*>(tile + (STAGED ? ti * g.iu : 0));
+    for (int e = threadIdx.x; e < 2 * tab; e += NT) {
+        const int h = e >= tab ? 1 : 0, k8 = 2 * (e - h * tab) + h;
+        int o = 0;
+        if (k8 < nk8) {
+            const int tap = g.nc8 == 1 ? k8 : (int)__umulhi(k8, g.mc), cu = k8 - tap * g.nc8;
+            const int dy = tap / 3, dx = tap - 3 * dy;
+            o = STAGED ? 16 * (dy * g.ru + dx * g.pu + cu) : (cu << 4) | tap;
+        }
+        steps[e] = o;
+    }
+    // this lane's pixel of each fragment
+    int base[PF], row0[PF], col0[PF];
+    long long pix[PF];                                   // pixel index, -1 outside
+#pragma unroll
+    for (int f = 0; f < PF; ++f) {
+        const int q = (wp * PF + f) * 32 + l32;
+        if (one) {
+            const int m = 64 * tl + q;
+            base[f] = (q >> 3) * g.ru + (q & 7) * g.pu;
+            pix[f] = m < a.M ? m : -1;
+            row0[f] = col0[f] = 0;
+        } else {
+            const int tx = q & ((1 << g.tw_log) - 1), ty = (q >> g.tw_log) & ((1 << g.th_log) - 1);
+            const int im = q >> (g.tw_log + g.th_log), b = b0 + im, y = y0 + ty, x = x0 + tx;
+            base[f] = im * g.iu + ty * g.ru + tx * g.pu;
+            pix[f] = b < a.nb && y < a.H && x < a.W ? (long long)(b * a.H + y) * a.W + x : -1;
+            row0[f] = y;
+            col0[f] = x;
+        }
+    }
+    if (STAGED)
+#pragma unroll
+        for (int f = 0; f < PF; ++f) base[f] *= 16;
+    auto load_a = [&](bf16x8 (&fa)[PF], int o) {
+        if (STAGED) {
+#pragma unroll
+            for (int f = 0; f < PF; ++f)
+                fa[f] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(tile) + base[f] + o);
+        } else {
+            const int cu = o >> 4, tap = o & 15, dy = tap / 3 - 1, dx = tap - 3 * (tap / 3) - 1;
+#pragma unroll
+            for (int f = 0; f < PF; ++f) {
+                uint4 v = make_uint4(0, 0, 0, 0);
+                const int y = one ? 0 : row0[f] + dy, x = one ? 0 : col0[f] + dx;
+                const bool in = pix[f] >= 0 &&
+                                (one || ((unsigned)y < (unsigned)a.H && (unsigned)x < (unsigned)a.W));
+                const long long q = one ? pix[f] : pix[f] + (long long)dy * a.W + dx;
+                if (in) v = *reinterpret_cast<const uint4*>(a.src + q * a.src_ld + 8 * cu);
+                fa[f] = *reinterpret_cast<const bf16x8*>(&v);
+            }
+        }
+    };
+    const int nf = blockIdx.y * WN + wn, n0 = nf * 32;
+    const bool live = n0 < a.N;                          // wave-uniform
+    // weight fragments of steps s .. s + AHEAD - 1 (reads past the last
+    // step stay inside the padded weight buffer)
+    const bf16x8* wq = reinterpret_cast<const bf16x8*>(a.wmat) + (long long)(live ? nf : 0) * nsteps * 64;
+    bf16x8 wb[AHEAD];
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) wb[j] = wq[j * 64 + lane];
+    floatx16 acc[PF];
+#pragma unroll
+    for (int f = 0; f < PF; ++f)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[f][r] = 0.f;
+    __syncthreads();
+    if (!live) return;
+    auto mma = [&](const bf16x8& w, const bf16x8 (&fa)[PF]) {
+#pragma unroll
+        for (int f = 0; f < PF; ++f)
+            acc[f] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, fa[f], acc[f], 0, 0, 0)
+                          : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[f], w, acc[f], 0, 0, 0);
+    };
+    // Groups of AHEAD steps, straight-line: the next step's pixels are
+    // read and the weights AHEAD steps on are requested before a step's
+    // products (the scheduling barriers keep them there).
+    const int4* so = reinterpret_cast<const int4*>(steps + half * tab);
+    constexpr int G4 = AHEAD / 4;
+    int4 on[G4];
+    int oc[AHEAD];
+    bf16x8 fa[2][PF];
+#pragma unroll
+    for (int q = 0; q < G4; ++q) on[q] = so[q];
+    load_a(fa[0], on[0].x);
+    int s = 0;
+    auto take = [&] {                                    // this group's offsets; the next one's loads
+#pragma unroll
+        for (int q = 0; q < G4; ++q) {
+            oc[4 * q] = on[q].x;
+            oc[4 * q + 1] = on[q].y;
+            oc[4 * q + 2] = on[q].z;
+            oc[4 * q + 3] = on[q].w;
+        }
+        so += G4;
+#pragma unroll
+        for (int q = 0; q < G4; ++q) on[q] = so[q];
+    };
+    const int whole = nk8 >> 1;                          // steps wholly inside K
+    for (; s + AHEAD <= whole; s += AHEAD) {
+        take();
+        wq += AHEAD * 64;
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) {
+            load_a(fa[(j + 1) & 1], j + 1 < AHEAD ? oc[j + 1] : on[0].x);
+            const bf16x8 w = wb[j];
+            wb[j] = wq[j * 64 + lane];
+            __builtin_amdgcn_sched_barrier(0);
+            mma(w, fa[j & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    take();
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) {
+        if (s + j >= nsteps) break;                      // uniform
+        if (j + 1 < AHEAD) load_a(fa[(j + 1) & 1], oc[j + 1]);
+        if (s + j >= whole && half)                      // the upper half is past K
+#pragma unroll
+            for (int f = 0; f < PF; ++f) fa[j & 1][f] = bf16x8{};
+        mma(wb[j], fa[j & 1]);
+    }
+    if (!SWAP) {
+        const int col = n0 + l32;
+#pragma unroll
+        for (int f = 0; f < PF; ++f)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                // the pixel of accumulator row r is held by lane `row`
+                const int row = (r >> 2) * 8 + half * 4 + (r & 3);
+                const int m = __shfl((int)pix[f], row, 64);
+                if (m < 0 || col >= a.dst_n) continue;
+                reinterpret_cast<float*>(a.dst)[(long long)m * a.dst_ld + a.dst_off + col] = acc[f][r] + a.bias[col];
+            }
+        return;
+    }
+#pragma unroll
+    for (int f = 0; f < PF; ++f) {
+        unsigned h[8];                                   // outputs 8 (q / 2) + 4 half + 2 (q mod 2) + 0, 1
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int n = n0 + 8 * (q >> 1) + 4 * half + 2 * (q & 1);
+            float v0 = acc[f][2 * q], v1 = acc[f][2 * q + 1];
+            if (EPI == EPI_RELU) {
+                v0 = fmaxf(v0 + (n < a.N ? a.bias[n] : 0.f), 0.f);
+                v1 = fmaxf(v1 + (n < a.N ? a.bias[n + 1] : 0.f), 0.f);
+            }
+            h[q] = (unsigned)f2bf(v0) | ((unsigned)f2bf(v1) << 16);
+        }
+        // lanes l and l + 32 exchange so that each holds eight consecutive outputs
+#pragma unroll
+        for (int q = 0; q < 8; q += 4) {
+            const auto s0 = __builtin_amdgcn_permlane32_swap(h[q], h[q + 2], false, false);
+            const auto s1 = __builtin_amdgcn_permlane32_swap(h[q + 1], h[q + 3], false, false);
+            const int n = n0 + 8 * (q >> 1) + 8 * half;
+            if (pix[f] < 0 || n >= a.dst_n) continue;
+            uint4 v = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+            if (EPI == EPI_MASK) {
+                const uint4 mk = *reinterpret_cast<const uint4*>(a.mask + pix[f] * a.mask_ld + n);
+                float m[8];
+                unpack8(mk, m);
+                bf16_t* o = reinterpret_cast<bf16_t*>(&v);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = m[e] > 0.f ? o[e] : (bf16_t)0;
+            }
+            *reinterpret_cast<uint4*>(reinterpret_cast<bf16_t*>(a.dst) + pix[f] * a.dst_ld + a.dst_off + n) = v;
+        }
+    }
+}
+
+ConvGeom conv_geom(const ConvArgs& a) {
+    ConvGeom g{};
+    g.nc8 = a.cin / 8;
+    if (a.taps == 1) {
+        g.th_log = g.tw_log = 3;
+        g.bw = g.bh = 8;
+        g.ntx = (a.M + 63) / 64;
+        g.nty = 1;
+    } else {
+        // small images share a tile: the least power of two that holds a side
+        auto lg = [](int n) { return n > 4 ? 3 : n > 2 ? 2 : n > 1 ? 1 : 0; };
+        g.th_log = lg(a.H);
+        g.tw_log = lg(a.W);
+        g.bw = (1 << g.tw_log) + 2;
+        g.bh = (1 << g.th_log) + 2;
+        g.ntx = (a.W + (1 << g.tw_log) - 1) >> g.tw_log;
+        g.nty = (a.H + (1 << g.th_log) - 1) >> g.th_log;
+    }
+    g.pu = g.nc8 | 1;
+    g.ru = g.bw * g.pu;
+    g.ru += (24 - (g.ru & 15)) & 15;
+    g.iu = g.bh * g.ru;
+    const int ti = 64 >> (g.th_log + g.tw_log);
+    g.entries = ti * g.bh * g.bw * g.nc8;
+    auto rec = [](int d) { return (unsigned)(((1ull << 32) + d - 1) / d); };
+    g.mc = rec(g.nc8);
+    g.mw = rec(g.bw);
+    g.mh = rec(g.bh);
+    return g;
+}
+
+template <int PF, int WP, int WN, int AHEAD, int EPI>
+void conv_launch_a(const ConvArgs& a, const ConvGeom& g, hipStream_t st) {
+    const int ti = 64 >> (g.th_log + g.tw_log);
+    const size_t tab = 8 * (size_t)conv_table((a.K + 15) / 16, AHEAD), lds = 16 * (size_t)ti * g.iu + tab;
+    const unsigned tiles = a.taps == 1 ? g.ntx : (unsigned)((a.nb + ti - 1) / ti * g.ntx * g.nty);
+    const dim3 grid(tiles, ((a.N + 31) / 32 + WN - 1) / WN), block(64 * WP * WN);
+    // (the reciprocals need e < 2^16)
+    if (lds <= kConvLds && g.entries < 65536)
+        hipLaunchKernelGGL((k_conv<PF, WP, WN, AHEAD, true, EPI>), grid, block, lds, st, a, g);
+    else
+        hipLaunchKernelGGL((k_conv<PF, WP, WN, AHEAD, false, EPI>), grid, block, tab, st, a, g);
+}
+
+template <int PF, int WP, int WN, int EPI>
+void conv_launch(const ConvArgs& a, const ConvGeom& g, hipStream_t st) {
+    if (a.K >= 16 * kConvAhead) conv_launch_a<PF, WP, WN, kConvAhead, EPI>(a, g, st);
+    else conv_launch_a<PF, WP, WN, 4, EPI>(a, g, st);
+}
+
+template <int EPI>
+void conv_dispatch(const ConvArgs& a, hipStream_t st) {
+    const ConvGeom g = conv_geom(a);
+    const int ti = 64 >> (g.th_log + g.tw_log), nf = (a.N + 31) / 32;
+    const long long tiles = a.taps == 1 ? g.ntx : (long long)((a.nb + ti - 1) / ti) * g.ntx * g.nty;
+    // Few fragments: a wave each (half the serial K loop per wave); many: two
+    // pixel fragments per wave (a weight fragment loaded serves both).  Waves
+    // along the outputs share the staged tile, as long as blocks remain for
+    // every compute unit.
+    if (tiles * nf < 1024 || nf == 1) {
+        if (nf >= 2 && tiles * nf >= 512) conv_launch<1, 2, 2, EPI>(a, g, st);
+        else conv_launch<1, 2, 1, EPI>(a, g, st);
+    } else if (nf >= 4 && tiles * nf >= 2048) {
+        conv_launch<2, 1, 4, EPI>(a, g, st);
+    } else {
+        conv_launch<2, 1, 2, EPI>(a, g, st);
+    }
+}
+
+// ---- weight gradients ------------------------------------------------------
 
 // Eight consecutive rows i0..i0+7 (one tap, channels c..c+7, or the ones row)
 // of the weight-gradient operand at pixel q.
@@ -79,11 +412,8 @@ __device__ inline uint4 wgrad_gather(const ConvArgs& a, int i0, int q, int k_end
 // Block tile BM x BN, four waves of 32 x 32 each (WN = BN / 32 along N).
 // Per K stage the block stages A (BM x BK) and B (BN x BK) in LDS with K
 // contiguous; a wave issues BK / 16 MFMA 32x32x16 on its sub-tile.
-// Lane l of a wave holds A rows (l mod 32), K entries 8 (l / 32) + 0..7; the
-// accumulator entry r of lane l is row 8 (r / 4) + 4 (l / 32) + r mod 4,
-// column l mod 32.
-template <int BM, int BN, int MODE, int EPI>
-__global__ void __launch_bounds__(kThreads) k_conv(ConvArgs a) {
+template <int BM, int BN>
+__global__ void __launch_bounds__(kThreads) k_wgrad(ConvArgs a) {
     static_assert(BM * BN == 4 * 32 * 32, "four 32x32 wave tiles");
     __shared__ __attribute__((aligned(16))) bf16_t As[BM * LDK];
     __shared__ __attribute__((aligned(16))) bf16_t Bs[BN * LDK];
@@ -91,50 +421,29 @@ __global__ void __launch_bounds__(kThreads) k_conv(ConvArgs a) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
-    int k_begin = 0, k_end = a.K;
-    if (MODE == MODE_WGRAD) {
-        k_begin = blockIdx.z * a.ksplit;
-        k_end = min(a.K, k_begin + a.ksplit);
-    }
+    const int k_begin = blockIdx.z * a.ksplit, k_end = min(a.K, k_begin + a.ksplit);
     floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 
     for (int k0 = k_begin; k0 < k_end; k0 += BK) {
-        if (MODE == MODE_CONV) {
 #pragma unroll
-            for (int e = t; e < BM * BK / 8; e += kThreads) {
-                const int i = e / (BK / 8), kr = (e % (BK / 8)) * 8;
-                const uint4 v = conv_gather(a, m0 + i, k0 + kr, k_end);
-                *reinterpret_cast<uint4*>(&As[i * LDK + kr]) = v;
-            }
+        for (int e = t; e < BM * BK / 8; e += kThreads) {
+            const int kk = e / (BM / 8), ir = (e % (BM / 8)) * 8;
+            const uint4 v = wgrad_gather(a, m0 + ir, k0 + kk, k_end);
+            const bf16_t* h = reinterpret_cast<const bf16_t*>(&v);
 #pragma unroll
-            for (int e = t; e < BN * BK / 8; e += kThreads) {
-                const int j = e / (BK / 8), kr = (e % (BK / 8)) * 8;
-                uint4 v = make_uint4(0, 0, 0, 0);
-                if (n0 + j < a.N && k0 + kr < k_end)
-                    v = *reinterpret_cast<const uint4*>(a.wmat + (long long)(n0 + j) * a.K + k0 + kr);
-                *reinterpret_cast<uint4*>(&Bs[j * LDK + kr]) = v;
-            }
-        } else {
+            for (int q = 0; q < 8; ++q) As[(ir + q) * LDK + kk] = h[q];
+        }
 #pragma unroll
-            for (int e = t; e < BM * BK / 8; e += kThreads) {
-                const int kk = e / (BM / 8), ir = (e % (BM / 8)) * 8;
-                const uint4 v = wgrad_gather(a, m0 + ir, k0 + kk, k_end);
-                const bf16_t* h = reinterpret_cast<const bf16_t*>(&v);
+        for (int e = t; e < BN * BK / 8; e += kThreads) {
+            const int kk = e / (BN / 8), jr = (e % (BN / 8)) * 8;
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (k0 + kk < k_end && n0 + jr < a.N)
+                v = *reinterpret_cast<const uint4*>(a.dz + (long long)(k0 + kk) * a.dz_ld + n0 + jr);
+            const bf16_t* h = reinterpret_cast<const bf16_t*>(&v);
 #pragma unroll
-                for (int q = 0; q < 8; ++q) As[(ir + q) * LDK + kk] = h[q];
-            }
-#pragma unroll
-            for (int e = t; e < BN * BK / 8; e += kThreads) {
-                const int kk = e / (BN / 8), jr = (e % (BN / 8)) * 8;
-                uint4 v = make_uint4(0, 0, 0, 0);
-                if (k0 + kk < k_end && n0 + jr < a.N)
-                    v = *reinterpret_cast<const uint4*>(a.dz + (long long)(k0 + kk) * a.dz_ld + n0 + jr);
-                const bf16_t* h = reinterpret_cast<const bf16_t*>(&v);
-#pragma unroll
-                for (int q = 0; q < 8; ++q) Bs[(jr + q) * LDK + kk] = h[q];
-            }
+            for (int q = 0; q < 8; ++q) Bs[(jr + q) * LDK + kk] = h[q];
         }
         __syncthreads();
 #pragma unroll
@@ -152,41 +461,7 @@ __global__ void __launch_bounds__(kThreads) k_conv(ConvArgs a) {
     for (int r = 0; r < 16; ++r) {
         const int row = m0 + wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
         if (row >= a.M || col >= a.dst_n) continue;
-        float v = acc[r];
-        if (EPI == EPI_PART) {
-            reinterpret_cast<float*>(a.dst)[((long long)blockIdx.z * a.M + row) * a.N + col] = v;
-            continue;
-        }
-        const long long o = (long long)row * a.dst_ld + a.dst_off + col;
-        if (EPI == EPI_RELU || EPI == EPI_F32) v += a.bias[col];
-        if (EPI == EPI_RELU) v = fmaxf(v, 0.f);
-        if (EPI == EPI_MASK && !(bf2f(a.mask[(long long)row * a.mask_ld + col]) > 0.f)) v = 0.f;
-        if (EPI == EPI_F32)
-            reinterpret_cast<float*>(a.dst)[o] = v;
-        else
-            reinterpret_cast<bf16_t*>(a.dst)[o] = f2bf(v);
-    }
-}
-
-template <int BM, int BN>
-void conv_dispatch(const ConvArgs& a, int mode, int epi, dim3 grid, hipStream_t st) {
-    if (mode == MODE_WGRAD) {
-        hipLaunchKernelGGL((k_conv<BM, BN, MODE_WGRAD, EPI_PART>), grid, dim3(kThreads), 0, st, a);
-        return;
-    }
-    switch (epi) {
-        case EPI_RELU:
-            hipLaunchKernelGGL((k_conv<BM, BN, MODE_CONV, EPI_RELU>), grid, dim3(kThreads), 0, st, a);
-            break;
-        case EPI_F32:
-            hipLaunchKernelGGL((k_conv<BM, BN, MODE_CONV, EPI_F32>), grid, dim3(kThreads), 0, st, a);
-            break;
-        case EPI_PLAIN:
-            hipLaunchKernelGGL((k_conv<BM, BN, MODE_CONV, EPI_PLAIN>), grid, dim3(kThreads), 0, st, a);
-            break;
-        default:
-            hipLaunchKernelGGL((k_conv<BM, BN, MODE_CONV, EPI_MASK>), grid, dim3(kThreads), 0, st, a);
-            break;
+        reinterpret_cast<float*>(a.dst)[((long long)blockIdx.z * a.M + row) * a.N + col] = acc[r];
     }
 }
 
@@ -367,19 +642,30 @@ __global__ void __launch_bounds__(kThreads) k_adam(float* p, float* m, float* v,
     p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
-// BF16 copies of one layer's weights w[tap][ci][co]: wf[co][tap][ci] for the
-// forward GEMM and wb[ci][taps-1-tap][co] for the input-gradient GEMM.
+// BF16 copies of one layer's weights w[tap][ci][co] in the fragment order of
+// k_conv: fragment (output group of 32, step of 16 K entries) is 64 lanes x 8
+// entries, lane l holding K entries 8 (l / 32) + 0..7 of output l mod 32; zeros
+// past the outputs and past K.  wf for the forward GEMM (outputs co, K = (tap,
+// ci)), wb for the input gradient (outputs ci, K = (flipped tap, co)).
 __global__ void __launch_bounds__(kThreads) k_export(const float* w, int taps, int cin, int cout,
                                                     bf16_t* wf, bf16_t* wb) {
-    const long long n = (long long)taps * cin * cout;
-    const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= n) return;
-    const int co = (int)(i % cout);
-    const int ci = (int)((i / cout) % cin);
-    const int tap = (int)(i / ((long long)cout * cin));
-    const bf16_t h = f2bf(w[i]);
-    wf[((long long)co * taps + tap) * cin + ci] = h;
-    wb[((long long)ci * taps + (taps - 1 - tap)) * cout + co] = h;
+    const long long nff = frag_elems(cout, taps * cin), nfb = frag_elems(cin, taps * cout);
+    long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
+    const bool back = i >= nff;
+    if (back) i -= nff;
+    if (back && i >= nfb) return;
+    const int N = back ? cin : cout, kc = back ? cout : cin, K = taps * kc;
+    const int nsteps = (K + 15) / 16;
+    const int e = (int)(i & 7), l = (int)(i >> 3) & 63;
+    const int fs = (int)(i >> 9), f = fs / nsteps, s = fs - f * nsteps;
+    const int n = 32 * f + (l & 31), k = 16 * s + 8 * (l >> 5) + e;
+    bf16_t h = 0;
+    if (n < N && k < K) {
+        const int tap = k / kc, c = k - tap * kc;
+        const int ci = back ? n : c, co = back ? c : n, t = back ? taps - 1 - tap : tap;
+        h = f2bf(w[((long long)t * cin + ci) * cout + co]);
+    }
+    (back ? wb : wf)[i] = h;
 }
 
 // One layer between the flat exchange layout (cin_o, cout_o) and the padded
@@ -721,15 +1007,22 @@ inline unsigned blocks(long long n) { return (unsigned)((n + kThreads - 1) / kTh
 
 }  // namespace
 
-void launch_conv(const ConvArgs& a, int mode, int epi, int splits, hipStream_t st) {
-    const bool narrow = a.N <= 32;
-    if (narrow) {
-        const dim3 grid((a.M + 127) / 128, (a.N + 31) / 32, mode == MODE_WGRAD ? splits : 1);
-        conv_dispatch<128, 32>(a, mode, epi, grid, st);
-    } else {
-        const dim3 grid((a.M + 63) / 64, (a.N + 63) / 64, mode == MODE_WGRAD ? splits : 1);
-        conv_dispatch<64, 64>(a, mode, epi, grid, st);
+void launch_conv(const ConvArgs& a, int epi, hipStream_t st) {
+    switch (epi) {
+        case EPI_RELU: conv_dispatch<EPI_RELU>(a, st); break;
+        case EPI_F32: conv_dispatch<EPI_F32>(a, st); break;
+        case EPI_PLAIN: conv_dispatch<EPI_PLAIN>(a, st); break;
+        default: conv_dispatch<EPI_MASK>(a, st); break;
     }
+}
+
+void launch_wgrad(const ConvArgs& a, int splits, hipStream_t st) {
+    if (a.N <= 32)
+        hipLaunchKernelGGL((k_wgrad<128, 32>), dim3((a.M + 127) / 128, (a.N + 31) / 32, splits),
+                           dim3(kThreads), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_wgrad<64, 64>), dim3((a.M + 63) / 64, (a.N + 63) / 64, splits),
+                           dim3(kThreads), 0, st, a);
 }
 
 void launch_wgrad_reduce(const float* part, int splits, int M, int N, float* out, hipStream_t st) {
@@ -792,7 +1085,7 @@ void launch_adam(float* p, float* m, float* v, const float* g, long long n, floa
 
 void launch_export(const float* w, int taps, int cin, int cout, bf16_t* wf, bf16_t* wb,
                    hipStream_t st) {
-    const long long n = (long long)taps * cin * cout;
+    const long long n = frag_elems(cout, taps * cin) + frag_elems(cin, taps * cout);
     hipLaunchKernelGGL(k_export, dim3(blocks(n)), dim3(kThreads), 0, st, w, taps, cin, cout, wf, wb);
 }
 

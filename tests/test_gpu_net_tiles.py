@@ -76,3 +76,49 @@ def test_layout_maps_at_tile_edges(N, X, Y, C, P, nb, with_base):
     np.testing.assert_allclose(F2.cpu().numpy()[:, 1:P], lin + back[:, :C * (P - 1)].reshape(nb, P - 1, C, Y, X), rtol=0, atol=1e-6)
     got = back[:, C * (P - 1):].reshape(nb, 3, P, C, Y, X)
     np.testing.assert_allclose(M2.cpu().numpy(), np.moveaxis(got, 1, 0), rtol=0, atol=1e-6)
+
+
+# H, W, in, out, base, levels, batch: images smaller than the 8 x 8 tile and
+# sharing it (an odd count of them), tiles cut by the image, 8 channels (a step
+# spans two taps), 24 and 104 channels (steps straddle taps), one fragment and
+# many, outputs past a fragment, and more channels than a staged tile holds
+NETS = [
+    (4, 4, 3, 5, 8, 2, 5),
+    (2, 6, 8, 9, 8, 1, 3),
+    (12, 20, 20, 40, 24, 2, 2),
+    (16, 8, 100, 70, 16, 3, 3),
+    (24, 24, 35, 33, 40, 2, 9),
+    (8, 8, 1000, 8, 8, 1, 1),
+]
+
+
+@pytest.mark.parametrize("case", NETS, ids=lambda c: "x".join(map(str, c)))
+def test_convolution_tiles_match_oracle(N, case):
+    import torch
+    H, W, cin, cout, base, levels, nb = case
+    print(f"net {case}", flush=True)
+    d = N.ot_net_default_desc(64, 64, cin, cout, nb)      # (checks its sizes for four levels)
+    d.H, d.W, d.base, d.levels = H, W, base, levels
+    specs = nn.layer_specs(cin, cout, base, levels)
+    rng = np.random.default_rng(cin + cout)
+    flat = nn.he_init(specs, 5) + 0.02 * rng.standard_normal(nn.param_count(specs))
+    params = nn.unflatten(specs, flat)
+    flat = np.concatenate([np.concatenate([_bf16(Wt).ravel(), np.float32(b).astype(np.float64)])
+                           for Wt, b in (params[s[0]] for s in specs)])
+    params = nn.unflatten(specs, flat)
+    x = _bf16(rng.uniform(0.0, 2.0, size=(nb, H, W, cin)))
+    t = rng.standard_normal((nb, H, W, cout))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).to("cuda:0")
+    net = N.Net(d, "cuda:0")
+    net.set_params(dev(flat))
+    rel = lambda a, b: float(np.linalg.norm(a - b) / np.linalg.norm(b))
+    y = net.forward(dev(x)).cpu().numpy()
+    assert rel(y, nn.forward(specs, params, x, levels)) < 2e-2
+    y1 = net.forward(dev(x[:1])).cpu().numpy()       # a smaller batch through the same net
+    np.testing.assert_array_equal(y1[0], y[0])
+    loss, g = net.grad(dev(x), dev(t), dev(np.ones(cout) / cout))
+    L, grads = nn.backward(specs, params, x, t, [(c, c + 1, 1.0 / cout) for c in range(cout)], levels)
+    assert abs(loss - L) <= 2e-2 * abs(L)
+    g, gr = g.cpu().numpy().astype(np.float64), nn.flatten_grads(specs, grads)
+    assert g @ gr / (np.linalg.norm(g) * np.linalg.norm(gr)) > 0.999
+    net.close()
