@@ -85,21 +85,6 @@ int check_desc(const ot_net_desc* d) {
     return OT_OK;
 }
 
-// Split of a weight-gradient GEMM over the pixels.
-// `bound` is an upper bound of `splits` over every K up to the one given.
-struct Split {
-    int splits, ksplit, bound;
-};
-Split wgrad_split(int M, int N, int K) {
-    const int bm = N <= 32 ? 128 : 64, bn = N <= 32 ? 32 : 64;
-    const long long tiles = (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-    int s = (int)std::max(1LL, (1024 + tiles - 1) / tiles);
-    s = std::min(s, std::max(1, K / 256));
-    int ks = (K + s - 1) / s;
-    ks = (ks + 31) / 32 * 32;
-    return {(K + ks - 1) / ks, ks, s};
-}
-
 }  // namespace
 
 struct ot_net {
@@ -187,10 +172,9 @@ size_t carve(const ot_net_desc& d, ot_net* n, char* base) {
         if (i < (size_t)2 * L) lev = (int)i / 2;
         else if (i + 1 < layers.size()) lev = L - 2 - (int)(i - 2 * L) / 2;
         else lev = 0;
-        const int K = (int)(B * (d.H >> lev) * (d.W >> lev));
         const int M = ly.taps * ly.cin_p + 1;
-        const Split s = wgrad_split(M, ly.cout_p, K);
-        cap = std::max(cap, (long long)s.bound * M * ly.cout_p);
+        const int splits = wgrad_splits(ly.taps, ly.cin_p, ly.cout_p, (int)B, d.H >> lev, d.W >> lev);
+        cap = std::max(cap, (long long)splits * M * ly.cout_p);
     }
     float* part = (float*)take(cap * 4);
     const int lb = loss_blocks(P0 * coutp);
@@ -304,17 +288,16 @@ int conv_wgrad(ot_net* n, int li, int nb, int lev, View src, const bf16_t* dz) {
     a.M = l.taps * l.cin_p + 1;
     a.N = l.cout_p;
     a.K = nb * a.H * a.W;
-    const Split s = wgrad_split(a.M, a.N, a.K);
-    if ((long long)s.splits * a.M * a.N > n->part_cap) {
+    const int splits = wgrad_splits(a.taps, a.cin, a.N, nb, a.H, a.W);
+    if ((long long)splits * a.M * a.N > n->part_cap) {
         n->err = "internal: weight-gradient partials exceed the workspace";
         return OT_ERR_SHAPE;
     }
-    a.ksplit = s.ksplit;
     a.dst = n->part;
     a.dst_ld = a.N;
     a.dst_n = a.N;
-    launch_wgrad(a, s.splits, n->st);
-    launch_wgrad_reduce(n->part, s.splits, a.M, a.N, n->grad + l.off_p, n->st);
+    launch_wgrad(a, splits, n->st);
+    launch_wgrad_reduce(n->part, splits, a.M, a.N, n->grad + l.off_p, n->st);
     return OT_OK;
 }
 

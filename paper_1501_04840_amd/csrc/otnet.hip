@@ -13,8 +13,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kThreads = 256;
-constexpr int BK = 32;          // K depth of one LDS stage
-constexpr int LDK = BK + 8;     // LDS row pitch (elements): 80 bytes
 
 // Round to nearest even (finite inputs).
 __device__ inline bf16_t f2bf(float f) {
@@ -386,92 +384,343 @@ void conv_dispatch(const ConvArgs& a, hipStream_t st) {
 }
 
 // ---- weight gradients ------------------------------------------------------
+//
+// dW[(tap, c)][n] = sum over pixels q of src[q + tap][c] dz[q][n]: the
+// contraction runs over pixels, while both tensors hold channels together.  A
+// block walks tiles of 64 pixels (as k_conv's); it stages the tile with its
+// border (the channels its rows need) and the tile's dz in LDS as they are and
+// reads both operands with transposing LDS loads (four pixels x 16 channels per
+// 16 lanes), so every tap reads the one staged tile.  Its 32 x 32 fragments of
+// dW, MW x NW per wave, stay in registers over all of its tiles, and the next
+// tile's loads are in flight during a tile's products.  Gathering each of the
+// nine taps' pixels and writing them to LDS transposed element by element took
+// 880 us for the 64 x 64 network and 32 images (67 TFLOP/s); this form 385 us
+// (152 TFLOP/s): 64 us for the widest layer, 15-43 us for the others, of which
+// the first tile's decoding and loads and the partial's stores are 8-10 us.
+//
+// Rows of dW are numbered i = (c / 32) taps + tap (fragments of 32 channels);
+// the bias gradient is a product with a row of ones, on the last wave of the
+// first row group.  NWAVE: the waves split the outputs instead of the rows
+// (1x1 layers: one or two row fragments, many outputs).
+typedef short short4v __attribute__((ext_vector_type(4)));
+typedef short short8v __attribute__((ext_vector_type(8)));
 
-// Eight consecutive rows i0..i0+7 (one tap, channels c..c+7, or the ones row)
-// of the weight-gradient operand at pixel q.
-__device__ inline uint4 wgrad_gather(const ConvArgs& a, int i0, int q, int k_end) {
-    uint4 v = make_uint4(0, 0, 0, 0);
-    const int rows = a.taps * a.cin;
-    if (q >= k_end || i0 > rows) return v;
-    if (i0 == rows) {                       // bias row: (1, 0, ..., 0)
-        v.x = 0x3F80u;
-        return v;
-    }
-    const int tap = i0 / a.cin, c = i0 - tap * a.cin;
-    const int hw = a.H * a.W;
-    const int b = q / hw, r = q - b * hw;
-    int y = r / a.W, x = r - (r / a.W) * a.W;
-    if (a.taps == 9) {
-        y += tap / 3 - 1;
-        x += tap % 3 - 1;
-        if (y < 0 || y >= a.H || x < 0 || x >= a.W) return v;
-    }
-    return *reinterpret_cast<const uint4*>(a.src + ((long long)(b * a.H + y) * a.W + x) * a.src_ld + c);
+struct WgradGeom {
+    int th_log, tw_log, ti;    // tile rows, columns and images (3x3 layers)
+    int bw, bh;                // staged columns and rows of one image
+    int ntx, nty, tiles;       // tiles along x and y, in all
+    unsigned mw, mh;           // reciprocals of bw and bh
+    int cf, mf;                // fragments of 32 channels, of 32 rows (cf taps)
+    int per_wave, group;       // row fragments per wave and block
+    int per_split;             // tiles per split
+};
+
+// Channel units of 8 staged by row group gy, and the first fragment's channel
+// fragment.
+__host__ __device__ inline int wgrad_units(const WgradGeom& g, int taps, int cin, int gy, int* cb0) {
+    const int f0 = gy * g.group, f1 = f0 + g.group < g.mf ? f0 + g.group : g.mf;
+    *cb0 = f0 / taps;
+    const int c1 = 32 * ((f1 - 1) / taps + 1);
+    return (c1 < cin ? c1 : cin) / 8 - 4 * *cb0;
+}
+// LDS pitch of a pixel of n units: 4 mod 8 units (64 bytes times an odd
+// number), so that the four pixels a transposing read takes from 32 lanes, 64
+// bytes each, fall in distinct banks, and at least n rounded up to whole
+// fragments of 4 units.
+__host__ __device__ inline int wgrad_pitch(int n) { return (n + 3) / 8 * 8 + 4; }
+
+__device__ __forceinline__ bf16x8 tr_read(const char* lds, int at0, int at1) {
+    typedef __attribute__((address_space(3))) short4v lds_short4;
+    const short4v x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(lds + at0));
+    const short4v y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(lds + at1));
+    const short8v v = __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, v);
 }
 
-// Block tile BM x BN, four waves of 32 x 32 each (WN = BN / 32 along N).
-// Per K stage the block stages A (BM x BK) and B (BN x BK) in LDS with K
-// contiguous; a wave issues BK / 16 MFMA 32x32x16 on its sub-tile.
-template <int BM, int BN>
-__global__ void __launch_bounds__(kThreads) k_wgrad(ConvArgs a) {
-    static_assert(BM * BN == 4 * 32 * 32, "four 32x32 wave tiles");
-    __shared__ __attribute__((aligned(16))) bf16_t As[BM * LDK];
-    __shared__ __attribute__((aligned(16))) bf16_t Bs[BN * LDK];
-    constexpr int WN = BN / 32;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-    const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
-    const int k_begin = blockIdx.z * a.ksplit, k_end = min(a.K, k_begin + a.ksplit);
-    floatx16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+// Q: units of a tile in flight per thread.  Where the accumulators leave room,
+// two waves share a SIMD.
+template <int MW, int NW, bool NWAVE, int Q>
+__global__ void __launch_bounds__(kThreads, Q < 12 && 16 * (MW + 1) * NW + 8 * Q <= 160 ? 2 : 1) k_wgrad(ConvArgs a, WgradGeom g) {
+    extern __shared__ __attribute__((aligned(16))) uint4 tile[];
+    constexpr int NB = NWAVE ? 4 * NW : NW;              // output fragments per block
+    const int lane = threadIdx.x & 63, half = lane >> 5, i16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool one = a.taps == 1;
+    const int gy = blockIdx.y, n0 = blockIdx.z * NB * 32;
+    int cb0;
+    const int nu = wgrad_units(g, a.taps, a.cin, gy, &cb0);
+    const int pu = wgrad_pitch(nu), ru = g.bw * pu, iu = g.bh * ru;
+    const int nd = min(a.N - n0, NB * 32) / 8, du = wgrad_pitch(nd);
+    const int dz0 = g.ti * iu;
+    const int es = g.ti * g.bh * g.bw * nu, ed = 64 * nd, entries = es + ed;
+    const unsigned mu = 0xFFFFFFFFu / nu + 1, md = 0xFFFFFFFFu / nd + 1;
+    const int t0 = blockIdx.x * g.per_split, t1 = min(t0 + g.per_split, g.tiles);
 
-    for (int k0 = k_begin; k0 < k_end; k0 += BK) {
+    // A thread's units of a tile, decoded once: LDS place (14 bits), border
+    // column (7), border row (4), image (6) and tensor (1: dz) in one word, and
+    // the element offset from the tile's origin.  A 1x1 layer is one image of
+    // one row of K pixels.
+    const int W = one ? a.K : a.W, H = one ? 1 : a.H;
+    unsigned pk[Q];
+    int rel[Q];
+    uint4 v[Q];
+    auto decode = [&](int e0) {
 #pragma unroll
-        for (int e = t; e < BM * BK / 8; e += kThreads) {
-            const int kk = e / (BM / 8), ir = (e % (BM / 8)) * 8;
-            const uint4 v = wgrad_gather(a, m0 + ir, k0 + kk, k_end);
-            const bf16_t* h = reinterpret_cast<const bf16_t*>(&v);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) As[(ir + q) * LDK + kk] = h[q];
+        for (int j = 0; j < Q; ++j) {
+            const int e = min(e0 + j * kThreads + (int)threadIdx.x, entries - 1);
+            int at, hx, hy, im, u;
+            const bool d = e >= es;
+            if (!d) {
+                const int px = nu == 1 ? e : (int)__umulhi(e, mu);
+                u = e - px * nu;
+                const int row = __umulhi(px, g.mw), col = px - row * g.bw;
+                im = one ? 0 : (int)__umulhi(row, g.mh);
+                hy = one ? 1 : row - im * g.bh;
+                hx = one ? px + 1 : col;
+                at = im * iu + (one ? row : hy) * ru + col * pu + u;
+            } else {
+                const int f = e - es, px = nd == 1 ? f : (int)__umulhi(f, md);
+                u = f - px * nd;
+                im = one ? 0 : px >> (g.tw_log + g.th_log);
+                hy = one ? 1 : ((px >> g.tw_log) & ((1 << g.th_log) - 1)) + 1;
+                hx = one ? px + 1 : (px & ((1 << g.tw_log) - 1)) + 1;
+                at = dz0 + px * du + u;
+            }
+            // images past the tile's (their pixels are zero) read no image
+            if (im >= g.ti) hx = 127;
+            pk[j] = (unsigned)at | (unsigned)hx << 14 | (unsigned)hy << 21 | (unsigned)im << 25 | (d ? 1u << 31 : 0u);
+            const int q = (im * H + hy - 1) * W + hx - 1;
+            rel[j] = q * (d ? a.dz_ld : a.src_ld) + 8 * u + (d ? n0 : 32 * cb0);
         }
-#pragma unroll
-        for (int e = t; e < BN * BK / 8; e += kThreads) {
-            const int kk = e / (BN / 8), jr = (e % (BN / 8)) * 8;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (k0 + kk < k_end && n0 + jr < a.N)
-                v = *reinterpret_cast<const uint4*>(a.dz + (long long)(k0 + kk) * a.dz_ld + n0 + jr);
-            const bf16_t* h = reinterpret_cast<const bf16_t*>(&v);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) Bs[(jr + q) * LDK + kk] = h[q];
+    };
+    unsigned inside = 0;
+    auto load = [&](int t) {
+        int b0 = 0, y0 = 0, x0 = 64 * t;
+        if (!one) {
+            const int per = g.ntx * g.nty, bi = t / per, r = t - bi * per;
+            b0 = bi * g.ti;
+            y0 = (r / g.ntx) << g.th_log;
+            x0 = (r % g.ntx) << g.tw_log;
         }
-        __syncthreads();
+        const long long q0 = (long long)(b0 * H + y0) * W + x0;
+        const bf16_t* const s0 = a.src + q0 * a.src_ld;
+        const bf16_t* const d0 = a.dz + q0 * a.dz_ld;
+        const int nim = one ? 1 : a.nb - b0;
+        inside = 0;
 #pragma unroll
-        for (int ks = 0; ks < BK; ks += 16) {
-            const int kq = ks + 8 * (lane >> 5);
-            const bf16x8 fa = *reinterpret_cast<const bf16x8*>(&As[(wm * 32 + (lane & 31)) * LDK + kq]);
-            const bf16x8 fb = *reinterpret_cast<const bf16x8*>(&Bs[(wn * 32 + (lane & 31)) * LDK + kq]);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, acc, 0, 0, 0);
+        for (int j = 0; j < Q; ++j) {
+            const int hx = pk[j] >> 14 & 127, hy = pk[j] >> 21 & 15, im = pk[j] >> 25 & 63;
+            const bool in = hx != 127 && im < nim && (unsigned)(y0 + hy - 1) < (unsigned)H &&
+                            (unsigned)(x0 + hx - 1) < (unsigned)W;
+            const bf16_t* s = (int)pk[j] < 0 ? d0 : s0;
+            v[j] = *reinterpret_cast<const uint4*>(in ? s + rel[j] : a.src);
+            inside |= in ? 1u << j : 0u;
         }
-        __syncthreads();
+    };
+    auto store = [&](int e0) {
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            if (e0 + j * kThreads + (int)threadIdx.x < entries)
+                tile[pk[j] & 16383] = inside >> j & 1 ? v[j] : make_uint4(0, 0, 0, 0);
+        }
+    };
+
+    // this lane's place in the transposing reads: pixel 16 ks + 8 half + 4 j +
+    // i16 / 4 of the tile, channels 16 ((lane / 16) mod 2) + 4 (i16 mod 4)
+    const int lch = 32 * ((lane >> 4) & 1) + 8 * (i16 & 3);   // bytes
+    int px[4][2];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int p = 16 * ks + 8 * half + 4 * j + (i16 >> 2);
+            int at;
+            if (one) {
+                at = (p >> 3) * ru + (p & 7) * pu;
+            } else {
+                const int tx = p & ((1 << g.tw_log) - 1), ty = (p >> g.tw_log) & ((1 << g.th_log) - 1);
+                const int im = p >> (g.tw_log + g.th_log);
+                at = im < g.ti ? im * iu + ty * ru + tx * pu : 0;
+            }
+            px[ks][j] = 16 * at + lch;
+        }
+    const int dzl = 16 * (dz0 + (8 * half + (i16 >> 2)) * du) + lch;
+    // byte offset of each row fragment: its tap and channels (past the last:
+    // some fragment's, not stored)
+    const int f0 = gy * g.group + (NWAVE ? 0 : wave * g.per_wave);
+    const int fend = min(min(f0 + g.per_wave, (gy + 1) * g.group), g.mf);
+    int foff[MW];
+#pragma unroll
+    for (int i = 0; i < MW; ++i) {
+        const int f = f0 + i < fend ? f0 + i : gy * g.group, cb = f / a.taps, tap = f - cb * a.taps;
+        foff[i] = 16 * ((tap / 3) * ru + (tap % 3) * pu + 4 * (cb - cb0));
     }
-
-    const int col = n0 + wn * 32 + (lane & 31);
+    const int nb0 = NWAVE ? wave * NW : 0;               // this wave's first output fragment
+    const int nlast = (nd + 3) / 4 - 1;                  // the block's last one with outputs
+    const bool bias = gy == 0 && (NWAVE || wave == 3);
+    floatx16 acc[MW][NW], accb[NW];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int row = m0 + wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-        if (row >= a.M || col >= a.dst_n) continue;
-        reinterpret_cast<float*>(a.dst)[((long long)blockIdx.z * a.M + row) * a.N + col] = acc[r];
+    for (int j = 0; j < NW; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            accb[j][r] = 0.f;
+#pragma unroll
+            for (int i = 0; i < MW; ++i) acc[i][j][r] = 0.f;
+        }
+    const __bf16 w1 = (lane & 31) == 0 ? (__bf16)1.f : (__bf16)0.f;
+    const bf16x8 ones = {w1, w1, w1, w1, w1, w1, w1, w1};
+    const char* const lds = reinterpret_cast<const char*>(tile);
+
+    const bool ahead = entries <= Q * kThreads;          // a tile's units all fit in registers
+    if (ahead) {
+        decode(0);
+        load(t0);
+    }
+    for (int t = t0; t < t1; ++t) {
+        if (t > t0) __syncthreads();                     // the last tile's reads are done
+        if (ahead) {
+            store(0);
+        } else {
+            for (int e0 = 0; e0 < entries; e0 += Q * kThreads) {
+                decode(e0);
+                load(t);
+                store(e0);
+            }
+        }
+        __syncthreads();
+        if (ahead && t + 1 < t1) load(t + 1);
+        // Steps n = ks MW + i; row fragments are read AH steps ahead and output
+        // fragments one ks ahead of their products (the scheduling barriers
+        // keep them there: left alone, every product waited for its own read).
+        constexpr int AH = 3;
+        bf16x8 fb[2][NW], fa[AH + 1];
+        auto read_b = [&](int ks) {
+#pragma unroll
+            for (int j = 0; j < NW; ++j) {
+                const int at = dzl + 64 * min(nb0 + j, nlast) + 256 * ks * du;
+                fb[ks & 1][j] = tr_read(lds, at, at + 64 * du);
+            }
+        };
+        auto read_a = [&](int n) {
+            const int ks = n / MW, i = n % MW;
+            fa[n % (AH + 1)] = tr_read(lds, px[ks][0] + foff[i], px[ks][1] + foff[i]);
+        };
+        read_b(0);
+#pragma unroll
+        for (int n = 0; n < AH; ++n) read_a(n);
+#pragma unroll
+        for (int n = 0; n < 4 * MW; ++n) {
+            const int ks = n / MW, i = n % MW;
+            if (i == 0 && ks < 3) read_b(ks + 1);
+            if (n + AH < 4 * MW) read_a(n + AH);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < NW; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[n % (AH + 1)], fb[ks & 1][j], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i == MW - 1 && bias)
+#pragma unroll
+                for (int j = 0; j < NW; ++j)
+                    accb[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, fb[ks & 1][j], accb[j], 0, 0, 0);
+        }
+    }
+    // partial of this split: rows tap cin + c, then the bias row
+    float* const out = reinterpret_cast<float*>(a.dst) + (long long)blockIdx.x * a.M * a.N;
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+        const int col = n0 + 32 * (nb0 + j) + (lane & 31);
+        if (col >= a.N) continue;
+#pragma unroll
+        for (int i = 0; i < MW; ++i) {
+            if (f0 + i >= fend) continue;
+            const int f = f0 + i, cb = f / a.taps, tap = f - cb * a.taps;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int c = 32 * cb + (r >> 2) * 8 + half * 4 + (r & 3);
+                if (c < a.cin) out[(long long)(tap * a.cin + c) * a.N + col] = acc[i][j][r];
+            }
+        }
+        if (bias && half == 0) out[(long long)(a.M - 1) * a.N + col] = accb[j][0];
     }
 }
 
-__global__ void __launch_bounds__(kThreads) k_wgrad_reduce(const float* part, int splits,
+// The wave tile of a layer: rows x outputs of 32 x 32 fragments.  Narrow
+// layers (32 outputs) keep up to 16 row fragments per wave, wider ones share
+// each row fragment read between two or four outputs; the row groups are
+// evened out, so that a block's waves all have work.
+struct WgradTile {
+    int mw, nw;
+    bool nwave;
+};
+WgradTile wgrad_tile(int taps, int cin, int cout) {
+    const int nf = (cout + 31) / 32, mf = taps * ((cin + 31) / 32);
+    if (taps == 1) return {1, 2, true};
+    if (nf == 1) return {mf <= 12 ? 3 : mf <= 28 ? 7 : 16, 1, false};
+    if (nf < 4) return {mf <= 12 ? 3 : mf <= 20 ? 5 : 7, 2, false};
+    return {3, 4, false};
+}
+
+WgradGeom wgrad_geom(int taps, int cin, int cout, int nb, int H, int W, int* row_groups,
+                     int* col_groups, size_t* lds) {
+    const WgradTile w = wgrad_tile(taps, cin, cout);
+    WgradGeom g{};
+    g.cf = (cin + 31) / 32;
+    g.mf = taps * g.cf;
+    const int cap = w.nwave ? w.mw : 4 * w.mw, ngr = (g.mf + cap - 1) / cap;
+    g.group = (g.mf + ngr - 1) / ngr;
+    g.per_wave = w.nwave ? g.group : (g.group + 3) / 4;
+    *row_groups = (g.mf + g.group - 1) / g.group;
+    const int NB = w.nwave ? 4 * w.nw : w.nw;
+    *col_groups = ((cout + 31) / 32 + NB - 1) / NB;
+    ConvArgs a{};
+    a.taps = taps; a.cin = cin; a.nb = nb; a.H = H; a.W = W; a.M = nb * H * W;
+    const ConvGeom c = conv_geom(a);
+    g.th_log = c.th_log; g.tw_log = c.tw_log; g.bw = c.bw; g.bh = c.bh;
+    g.ntx = c.ntx; g.nty = c.nty; g.mw = c.mw; g.mh = c.mh;
+    g.ti = taps == 1 ? 1 : 64 >> (g.th_log + g.tw_log);
+    const int nd = std::min((cout + 7) / 8, 4 * NB);
+    for (;;) {           // tiny images: as many per tile as LDS holds
+        size_t most = 0;
+        for (int gy = 0; gy < *row_groups; ++gy) {
+            int cb0;
+            const int nu = wgrad_units(g, taps, cin, gy, &cb0);
+            most = std::max(most, (size_t)g.ti * g.bh * g.bw * wgrad_pitch(nu));
+        }
+        *lds = 16 * (most + 64 * (size_t)wgrad_pitch(nd));
+        if (*lds <= kConvLds || g.ti == 1) break;
+        g.ti /= 2;
+    }
+    g.tiles = taps == 1 ? c.ntx : (nb + g.ti - 1) / g.ti * c.ntx * c.nty;
+    return g;
+}
+
+// Sum of the splits' partials: 64 consecutive entries per block, each wave
+// every fourth split with eight loads in flight (a thread per entry waiting on
+// its chain of up to 342 loads took 430 us over the layers of the 64 x 64
+// network; now 146).
+__global__ void __launch_bounds__(kThreads) k_wgrad_reduce(const float* __restrict__ part, int splits,
                                                           long long mn, float* out) {
-    const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= mn) return;
-    float s = 0.f;
-    for (int z = 0; z < splits; ++z) s += part[z * mn + i];
-    out[i] = s;
+    __shared__ float red[kThreads / 64][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    constexpr int NWV = kThreads / 64, U = 8;
+    const long long i = (long long)blockIdx.x * 64 + lane;
+    const float* s = part + (i < mn ? i : 0);
+    float acc = 0.f;
+    for (int z = w; z < splits; z += NWV * U) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = z + NWV * u < splits ? s[(z + NWV * u) * mn] : 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc += v[u];
+    }
+    red[w][lane] = acc;
+    __syncthreads();
+    if (w == 0 && i < mn) {
+        float t = red[0][lane];
+#pragma unroll
+        for (int q = 1; q < NWV; ++q) t += red[q][lane];
+        out[i] = t;
+    }
 }
 
 // BF16 copy of the FP32 input, channels padded to ld (a multiple of 8) with
@@ -1016,18 +1265,51 @@ void launch_conv(const ConvArgs& a, int epi, hipStream_t st) {
     }
 }
 
+// Splits of a layer's pixels: a block per compute unit where a wave's
+// fragments fill its registers, else two.
+int wgrad_splits(int taps, int cin, int cout, int nb, int H, int W) {
+    int rows, cols;
+    size_t lds;
+    const WgradGeom g = wgrad_geom(taps, cin, cout, nb, H, W, &rows, &cols, &lds);
+    const WgradTile w = wgrad_tile(taps, cin, cout);
+    const int most = std::max(1, (w.mw * w.nw > 8 ? 256 : 512) / (rows * cols));
+    return std::min(most, g.tiles);
+}
+
 void launch_wgrad(const ConvArgs& a, int splits, hipStream_t st) {
-    if (a.N <= 32)
-        hipLaunchKernelGGL((k_wgrad<128, 32>), dim3((a.M + 127) / 128, (a.N + 31) / 32, splits),
-                           dim3(kThreads), 0, st, a);
-    else
-        hipLaunchKernelGGL((k_wgrad<64, 64>), dim3((a.M + 63) / 64, (a.N + 63) / 64, splits),
-                           dim3(kThreads), 0, st, a);
+    int rows, cols;
+    size_t lds;
+    WgradGeom g = wgrad_geom(a.taps, a.cin, a.N, a.nb, a.H, a.W, &rows, &cols, &lds);
+    g.per_split = (g.tiles + splits - 1) / splits;
+    const WgradTile w = wgrad_tile(a.taps, a.cin, a.N);
+    const dim3 grid(splits, rows, cols), block(kThreads);
+    // units of the largest tile per thread: the variant that keeps them all in
+    // flight with the fewest idle loads
+    int most = 0;
+    for (int gy = 0; gy < rows; ++gy) {
+        int cb0;
+        most = std::max(most, g.ti * g.bh * g.bw * wgrad_units(g, a.taps, a.cin, gy, &cb0));
+    }
+    most += 64 * std::min(a.N / 8, 4 * (w.nwave ? 4 * w.nw : w.nw));
+#define OTN_WG(MW, NW, NWAVE, Q)                                                                  \
+    if (w.mw == MW && w.nw == NW && (most <= Q * kThreads || Q == 12)) {                          \
+        hipLaunchKernelGGL((k_wgrad<MW, NW, NWAVE, Q>), grid, block, lds, st, a, g);              \
+        return;                                                                                   \
+    }
+    OTN_WG(1, 2, true, 8) OTN_WG(1, 2, true, 12)
+    OTN_WG(3, 1, false, 4) OTN_WG(3, 1, false, 12)
+    OTN_WG(7, 1, false, 8) OTN_WG(7, 1, false, 12)
+    OTN_WG(16, 1, false, 12)
+    OTN_WG(3, 2, false, 4) OTN_WG(3, 2, false, 12)
+    OTN_WG(5, 2, false, 8) OTN_WG(5, 2, false, 12)
+    OTN_WG(7, 2, false, 8) OTN_WG(7, 2, false, 12)
+    OTN_WG(3, 4, false, 8) OTN_WG(3, 4, false, 12)
+#undef OTN_WG
 }
 
 void launch_wgrad_reduce(const float* part, int splits, int M, int N, float* out, hipStream_t st) {
     const long long mn = (long long)M * N;
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks(mn)), dim3(kThreads), 0, st, part, splits, mn, out);
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((mn + 63) / 64)), dim3(kThreads), 0, st, part, splits, mn, out);
 }
 
 void launch_pack_input(const float* x, int in_ch, long long npix, bf16_t* out, int ld,
