@@ -28,7 +28,7 @@ LIB_ASAN = os.path.join(OBJ_ASAN, "libotdyn_asan.so")
 SAN_FLAGS = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
              "-Xarch_host", "-fno-omit-frame-pointer", "-Xarch_host", "-fno-sanitize-recover=all"]
 
-SOURCES = ["stencil.hip", "stencil_rows.hip", "transform.hip", "fastdct.hip", "plan.cpp",
+SOURCES = ["stencil.hip", "stencil_rows.hip", "transform.hip", "fastdct.hip", "dense3.hip", "plan.cpp",
            "batch.cpp", "otnet.hip", "net.cpp", "hue.hip", "solve_static.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -10,36 +10,6 @@
 
 namespace otd {
 
-// Planes reduced per block by the plane-sum blocks of k_rows_fft (32 lanes,
-// half a wave, per plane).
-constexpr int kSumPlanesPerBlock = 8;
-
-// One plane-sum block: kSumPlanesPerBlock planes of `ps` (32 lanes, half a
-// wave, per plane) reduced in place into slot 0 of each plane.  No block
-// synchronisation: such blocks return independently.
-__device__ __forceinline__ void plane_sums_block(const PlaneSums& ps, long long blk) {
-    const int l = threadIdx.x & 31;
-    const long long q = blk * kSumPlanesPerBlock + (threadIdx.x >> 5);
-    const bool live = q < ps.nq;
-    double* pp = ps.part + (live ? q : 0) * ps.nbx;
-    double acc = 0.0;
-    for (int i = l; i < ps.nbx; i += 32 * 16) {
-        double v[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const int ii = i + 32 * u;
-            v[u] = live && ii < ps.nbx ? pp[ii] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < 16; ++u) acc += v[u];
-    }
-#pragma unroll
-    for (int off = 16; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 32);
-    // every lane's loads of this plane are consumed above, so slot 0 can be
-    // overwritten with the total
-    if (live && l == 0) pp[0] = acc;
-}
-
 // Contiguous axis: LPB whole rows per block, row pitch L + 1 in LDS.  The
 // block's rows are one contiguous span, staged with unrolled loads so that
 // every thread keeps all of its loads in flight at once; single floats,

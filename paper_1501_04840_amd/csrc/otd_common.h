@@ -137,6 +137,35 @@ struct PlaneSums {
     long long nq;
     int nbx;
 };
+// Planes reduced per block by the plane-sum blocks of the first forward pass (32 lanes,
+// half a wave, per plane).
+constexpr int kSumPlanesPerBlock = 8;
+
+// One plane-sum block: kSumPlanesPerBlock planes of `ps` (32 lanes, half a
+// wave, per plane) reduced in place into slot 0 of each plane.  No block
+// synchronisation: such blocks return independently.
+__device__ __forceinline__ void plane_sums_block(const PlaneSums& ps, long long blk) {
+    const int l = threadIdx.x & 31;
+    const long long q = blk * kSumPlanesPerBlock + (threadIdx.x >> 5);
+    const bool live = q < ps.nq;
+    double* pp = ps.part + (live ? q : 0) * ps.nbx;
+    double acc = 0.0;
+    for (int i = l; i < ps.nbx; i += 32 * 16) {
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int ii = i + 32 * u;
+            v[u] = live && ii < ps.nbx ? pp[ii] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) acc += v[u];
+    }
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 32);
+    // every lane's loads of this plane are consumed above, so slot 0 can be
+    // overwritten with the total
+    if (live && l == 0) pp[0] = acc;
+}
 // Rows of a row pass that belong to frozen problems: frz[b] nonzero for
 // problem b, rpp rows per problem (null frz: none).
 struct RowSkip {
@@ -183,6 +212,30 @@ void launch_fused_x(const Geom& g, float* R, float* Rt, const AxisTab& tx,
                     bool premixed, hipStream_t st);
 void launch_fused_yt(const Geom& g, float* Rt, const AxisTab& tx, const AxisTab& ty,
                      const AxisTab& tc, const AxisTab& tt, hipStream_t st);
+
+// Dense three-pass solve (dense3.hip) for x and y of any length up to 512 and P
+// <= 64.  An axis's matrices in fragment order: blocks of H positions (folded,
+// Neumann axes longer than 16: even and odd frequencies), H a multiple of 16.
+struct DenseAxis {
+    int H, fold;
+    const float* fwd;
+    const float* inv;
+};
+constexpr int kDenseAxisPad = 3;     // fragments (256 floats) of zeros behind the matrices
+bool dense_fold(int n, int periodic);
+int dense_width(int n, int periodic);
+size_t dense_axis_floats(int n, int periodic);
+// The fragments of M (orthonormal, M[frequency n + position]) into out.
+void dense_axis_fill(int n, int periodic, const double* M, float* out);
+DenseAxis dense_axis(int n, int periodic, const float* dev);
+bool dense3_ok(const Geom& g);
+// Pass 0 forward x into Rt ([B][X][C][Y][P]; it also reduces the plane sums of
+// r in part_slice in place), 1 y and time in place on Rt, 2 inverse x.  r is in
+// colour modes (StepArgs::cmix).  Problems with frz[b] nonzero are skipped.
+void launch_dense3(const Geom& g, float* R, float* Rt, const AxisTab& tx, const AxisTab& ty,
+                   const AxisTab& tc, const AxisTab& tt, const DenseAxis& ax, const DenseAxis& ay,
+                   const double* tc64, const double* tt64, double* part_slice, int nbx, int pass,
+                   const float* frz, hipStream_t st);
 
 // Whole Poisson solve of problems with one spatial axis (transform.hip):
 // Y = C = 1, P in {8, 16, 32}, X in {64, 128, 256} with its fast transform

@@ -32,6 +32,8 @@ struct ot_dyn_plan {
     float* Phi;              // carried potential (OT_REFINE_CARRY), else null
     float* Rt;               // fused Poisson passes: transposed scratch [B][C][X][Y][P]
     bool fused;              // the fused three-pass Poisson solve applies
+    bool dense3;             // the dense three-pass Poisson solve applies
+    DenseAxis dax[2];        // its matrices of x and y
     bool freezable;          // a batch group's plan: its problems can be frozen
     bool p1d;                // one spatial axis: the one-block Poisson solve applies
     bool xfold;              // the divergence kernels also do the forward x transform
@@ -91,7 +93,7 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
     size_t off_b, off_bb, off_A, off_R, off_R2, off_Phi, off_Rt, off_sig, off_f,
-        off_tab[4], off_tw[4], off_tc64, off_tt64;
+        off_tab[4], off_tw[4], off_dense[2], off_tc64, off_tt64;
     size_t off_pslice, off_pred, off_pdiv, off_pmass, off_pbnd, off_red;
     size_t total;
     int nbx, nbx_node, nblk_bnd;
@@ -162,6 +164,30 @@ int validate(const ot_dyn_desc* d, std::string* why) {
     return OT_OK;
 }
 
+// The dense three-pass solve is taken where the five passes would have a dense
+// one among them: a side without a fast or mixed-radix transform, or colours and
+// times without a register transform.  Us per iteration, five passes against
+// three: 173 x 131 x 3 x 12 128 and 80, 50 x 70 x 3 x 10 76 and 35,
+// 300 x 500 x 3 x 12 (periodic x) 2095 and 583, 173 x 64 x 3 x 16 71 and 50; fast
+// sides with P = 12 128 x 128 x 3 68 and 55, 180 x 100 x 3 x 20 122 and 98.  The
+// five passes stay for fast sides where the dense products grow with the sides
+// (P = 12: 256 x 256 x 3 143 and 156, 512 x 512 x 3 533 and 644; times and colours in
+// registers: 100 x 100 x 3 x 32 74 and 83, 360 x 100 x 3 x 32 periodic 191 and
+// 274); a fast side over 180 with times in registers (512 x 90 x 3 x 32 245 and
+// 309, 256 x 131 x 3 x 16 109 and 134); and many problems of a tile or two
+// (24 x 24 x 3 x 16, 64 of them, 113 and 121; 33 x 31 x 3 x 16, 32 of them, 118 and
+// 100; 16 x 16 x 3 x 12, 512 of them, 484 and 507).
+bool dense3_pays(const Geom& g) {
+    if (!dense3_ok(g)) return false;
+    const auto fast = [](int n) { return fast_len(n) || mix_len(n); };
+    const bool fx = fast(g.X), fy = fast(g.Y);
+    const bool times = (g.P == 8 || g.P == 16 || g.P == 32) && (g.C == 1 || g.C == 3);
+    const int side = times ? 40 : 16, rows = times ? 1024 : 4096;
+    if (std::max(g.X, g.Y) <= side && (long long)g.Y * g.B >= rows) return false;
+    if (!times) return !fx || !fy || g.X + g.Y <= 320;
+    return !(fx && fy) && !(fx && g.X > 180) && !(fy && g.Y > 180);
+}
+
 Layout layout_of(const ot_dyn_desc& d) {
     const Geom g = make_geom(d);
     Layout L;
@@ -182,6 +208,9 @@ Layout layout_of(const ot_dyn_desc& d) {
         L.off_tab[a] = take((2 * (size_t)ns[a] * ns[a] + ns[a]) * sizeof(float));
         L.off_tw[a] = take((4 * (size_t)ns[a] + ns[a] / 2) * 2 * sizeof(float));
     }
+    const bool dense = dense3_pays(g);
+    L.off_dense[0] = take(dense ? dense_axis_floats(d.X, g.perx) * sizeof(float) : 0);
+    L.off_dense[1] = take(dense ? dense_axis_floats(d.Y, g.pery) * sizeof(float) : 0);
     L.off_tc64 = take(((size_t)d.C * d.C + d.C) * sizeof(double));
     L.off_tt64 = take(((size_t)d.P * d.P + d.P) * sizeof(double));
     // FP64 partials: per-node kernels write one per 256 nodes of a plane; the
@@ -276,7 +305,7 @@ StepArgs step_args(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc) {
     s.row_bx = p->row_bx;
     s.twx = p->xfold ? p->tab[0].tw : nullptr;
     s.xkind = p->tab[0].periodic ? 2 : 0;
-    s.cmix = p->fused && p->g.C > 1 ? p->tab[2].mat : nullptr;
+    s.cmix = (p->fused || p->dense3) && p->g.C > 1 ? p->tab[2].mat : nullptr;
     s.nt_store = (long long)p->g.B * p->g.nc * (long long)sizeof(float) >= (16ll << 20) ? 1 : 0;
     return s;
 }
@@ -325,6 +354,16 @@ void poisson(ot_dyn_plan* p, float* R) {
             launch_fused_yt(g, p->Rt, p->tab[0], p->tab[1], p->tab[2], p->tab[3], st);
         });
         timed(p, OT_PHASE_XFORM_X, [&] { x_pass(1); });
+        return;
+    }
+    if (p->dense3) {
+        const int phase[3] = {OT_PHASE_XFORM_X, OT_PHASE_TC, OT_PHASE_XFORM_X};
+        for (int pass = 0; pass < 3; ++pass)
+            timed(p, phase[pass], [&] {
+                launch_dense3(g, R, p->Rt, p->tab[0], p->tab[1], p->tab[2], p->tab[3], p->dax[0],
+                              p->dax[1], p->tc64, p->tt64, p->part_slice, p->nbx, pass,
+                              p->freezable ? p->frz : nullptr, st);
+            });
         return;
     }
     // the first forward pass also reduces the FP64 plane sums of r that the
@@ -382,9 +421,10 @@ void apply_tuning(ot_dyn_plan* p, int row_bx, int dense_xy) {
     // problems with one spatial axis: the whole solve in one block per problem
     p->p1d = dense_xy != 1 && poisson_1d_ok(g, p->tab[0], p->tab[3]);
     p->fused = dense_xy == 0 && fused_poisson_ok(g, p->tab[0], p->tab[1], p->tab[3]);
+    p->dense3 = dense_xy == 0 && !p->p1d && !p->fused && dense3_pays(g);
     // the five-pass solve with rows of one block each: the divergence
     // kernels write r already transformed along x (one pass fewer)
-    p->xfold = !p->p1d && !p->fused && g.X > 1 && div_fold_ok(g, row_bx, p->tab[0]);
+    p->xfold = !p->p1d && !p->fused && !p->dense3 && g.X > 1 && div_fold_ok(g, row_bx, p->tab[0]);
 }
 
 bool refine_now(const ot_dyn_plan* p) {
@@ -751,6 +791,16 @@ int ot_dyn_create(const ot_dyn_desc* d, void* stream, void* workspace, size_t ws
             if (e != hipSuccess) { delete p; return OT_ERR_HIP; }
             if (fast) p->tab[a].tw = (const float2*)tdst;
             else p->tab[a].twm = (const float2*)tdst;
+        }
+        if (a < 2 && dense3_pays(p->g)) {
+            std::vector<float> hd(dense_axis_floats(n, per[a]));
+            dense_axis_fill(n, per[a], M.data(), hd.data());
+            float* ddst = (float*)(p->ws + L.off_dense[a]);
+            e = hipMemcpyAsync(ddst, hd.data(), hd.size() * sizeof(float), hipMemcpyHostToDevice,
+                               p->stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
+            if (e != hipSuccess) { delete p; return OT_ERR_HIP; }
+            p->dax[a] = dense_axis(n, per[a], ddst);
         }
         if (a < 2) { p->tw_fast[a] = p->tab[a].tw; p->tw_mix[a] = p->tab[a].twm; }
         if (a == 2 || a == 3) {
