@@ -65,11 +65,10 @@ int ot_hue_create(long long npix, int nbins, int max_frames, void* stream, void*
 void ot_hue_destroy(ot_hue* h);
 
 /* The source image (rgb: device, npix x 3 bytes): hues, bins, bin counts, the
- * strict order (a stable radix sort of 24-bit hue keys, three 8-bit passes)
- * and each pixel's rank in it.  The renderer keeps the pointer:
- * every later frame reads the image's max and min channels from it, so it
- * must stay allocated and unchanged until the last frame rendered from it is
- * done (or the next ot_hue_set_source).  Asynchronous.  OT_ERR_PARAM for a
+ * strict order (a stable radix sort of 19-bit hue keys in two passes), each
+ * pixel's rank in it and its max and min channels.  The image must stay
+ * allocated and unchanged until this work on the renderer's stream is done;
+ * the frames do not read it.  Asynchronous.  OT_ERR_PARAM for a
  * null pointer, OT_ERR_HIP if a launch fails. */
 int ot_hue_set_source(ot_hue* h, const unsigned char* rgb);
 

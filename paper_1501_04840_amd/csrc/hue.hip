@@ -3,21 +3,17 @@
 // density by exact circular histogram specification (the readings are listed
 // in ot_hue.h).
 //
-// Device layout (one caller-owned workspace, carved by ot_hue_create): the
-// hue bits, two sort-key buffers, two index buffers (the first also holds the
-// ranks) u32 [N], the radix histograms int32 [256][tiles] and their digit
-// totals, the source counts int32 [n]; per frame, the target counts and their
-// inclusive cumulative sums int32 [n] and the shift one int64.  The strict
-// order is a stable LSD radix sort of 24-bit keys written here: three passes
-// of 8 bits, each a histogram kernel, a scan kernel and a scatter kernel
-// whose blocks rank their tile stably in LDS (wave ballots per round) and
-// write every digit's run contiguously; the last pass writes each pixel's
-// rank instead of the order.  Per call of F frames: one planning
-// kernel of F blocks (target counts, median shift) and one streaming kernel
-// over the pixels in raster order with the frames along grid y, four pixels
-// per thread (reads 3 bytes of RGB, the 4-byte hue kept from the source's
-// sort keys and the 4-byte rank, writes 3 bytes and optionally the 4-byte
-// bin).
+// Device layout (one caller-owned workspace, carved by ot_hue_create), per
+// pixel: the hue FP32, the max and min channel 2 bytes, the rank u32, and for
+// the sort the position in the order of the low digit u32, the high digit u16
+// and the rank in that order u32; the digit counts per tile int32 [1024][tiles]
+// and their totals, the source counts int32 [n]; per frame, the target counts
+// and their inclusive cumulative sums int32 [n] and the shift one int64.  The
+// strict order is a stable radix sort of 19-bit keys in two passes (below).  Per
+// call of F frames: one planning kernel of F blocks (target counts, median
+// shift) and one streaming kernel over the pixels in raster order with the
+// frames along grid y, four pixels per thread (reads 10 bytes per pixel, writes
+// 3 and optionally the 4-byte bin).
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -32,18 +28,15 @@ constexpr int kMaxBins = 4096;
 constexpr long long kMaxPix = 1LL << 30;
 constexpr int kThreads = 256;
 constexpr int kPlanThreads = 1024;
-constexpr unsigned kKeyBlocks = 2048;     // 8 blocks per compute unit
 constexpr unsigned kRenderBlocks = 4096;  // 16 blocks per compute unit, per frame
 constexpr int kMaxFrames = 65535;         // frames per call (grid y)
 constexpr unsigned kConvBlocks = 8192;    // RGB<->HSV grid-stride launches
-// radix sort of the 24-bit hue keys: 3 passes of 8-bit digits over tiles of
-// kSortThreads x kSortItems keys
+// radix sort of the 19-bit hue keys over tiles of kSortThreads x kSortItems
 constexpr int kSortThreads = 512;
 constexpr int kSortItems = 16;
 constexpr int kSortTile = kSortThreads * kSortItems;
 constexpr int kSortWaves = kSortThreads / 64;
-constexpr int kRadix = 256;
-constexpr int kKeyBits = 24;
+constexpr int kKeyBits = 19;
 
 // Every FP32 step below is one rounded operation in the written order: no
 // contraction of a product and a sum into a fused multiply-add.
@@ -171,99 +164,138 @@ __global__ void k_fill_i32(int* p, int n, int v) {
     if (i < n) p[i] = v;
 }
 
-// Hue sort key (the FP32 bit pattern: monotone for hues >= 0), raster index,
-// and the bin histogram (per-block LDS counts over a grid-stride loop, then
-// one global add per bin and block).  Four pixels per thread; VEC: the image
-// is 4-byte aligned, so a group of four moves as one 12-byte load and two
-// 16-byte stores (the tail group and unaligned images go pixel by pixel).
-// Sort key: floor(h 2^24), exact (a power-of-two scaling).  Distinct hues of
-// 8-bit RGB differ by at least 1 / (6 * 255^2) (differences of fractions
-// with denominators <= 255, over 6), far above 2^-24 plus the few ulps of
-// their FP32 rounding, and equal hues give equal floats, so this 24-bit key
-// orders pixels exactly as the hue does, in three radix passes instead of
-// four.
+// Sort key: floor(h 2^19), exact (a power-of-two scaling).  Distinct hues of
+// 8-bit RGB differ by at least 1 / (6 * 255 * 254) (differences of fractions with
+// denominators <= 255, over 6), 1.34 * 2^-19: 2^-19 plus more than the few ulps of
+// their FP32 rounding.  Equal hues give equal floats.  So this 19-bit key orders
+// pixels exactly as the hue does.
 __device__ __forceinline__ unsigned sort_key(float h) {
-    return (unsigned)(h * 16777216.f);
+    return (unsigned)(h * (float)(1u << kKeyBits));
 }
 
+// ---- strict order of the pixels: a stable radix sort of the keys in two passes
+//
+// Tile i holds elements [i T, (i + 1) T) of the current order, T = kSortTile, and
+// wave w of its block the w-th eighth, 64 elements a round: the order (wave,
+// round, lane) is the element order.  Nothing but the rank of each pixel is
+// wanted, so no pixel index is ever moved:
+//   k_hue_keys      hues, bin counts, and per tile the counts of the low digit;
+//   k_sort_low      each pixel's position pos in the order of the low digit, and the high digits moved there
+//                   (2 bytes each, through LDS, in runs of a tile's equal digits);
+//   k_sort_hist     per tile of that order the counts of the high digit;
+//   k_sort_high     the rank of each element of that order, written there;
+//   k_sort_gather   rank[p] = that of position pos[p].
+// with k_sort_scan of the counts before k_sort_low and k_sort_high.  A wave counts
+// its own digits, so a round needs no barrier; tiles are dealt to the XCDs in
+// contiguous eighths, so that one L2 merges the short runs that adjacent tiles
+// write side by side.  3840 x 2160: keys 29 us, low 34, hist
+// 18, high 34, gather 28, the scans 5 each.  Three 8-bit passes that moved keys
+// and indices, with four barriers a round and the last pass's random 4-byte
+// writes, took 308 us (the scatters 232) after 47 us of keys.
+constexpr int kLowBits = 9, kLow = 1 << kLowBits;
+constexpr int kHigh = 1 << (kKeyBits - kLowBits);
+
+// The tile of a block: XCD j (blocks go round-robin) gets the j-th contiguous
+// eighth.
+__device__ __forceinline__ int tile_of(int hw, int ntiles) {
+    const int q = ntiles >> 3, r = ntiles & 7, xcd = hw & 7, slot = hw >> 3;
+    return xcd * q + min(xcd, r) + slot;
+}
+
+// Hue (FP32) and max and min channel (hilo) in raster order, bin histogram (LDS counts, then one global add per
+// bin and block) and the low digit's counts of a tile.  Four pixels per thread
+// and step; VEC: the image is 4-byte aligned, so a group of four moves as one
+// 12-byte load and one 16- and one 8-byte store (the tail group and unaligned images go
+// pixel by pixel).
 template <bool VEC>
-__global__ void __launch_bounds__(kThreads) k_hue_keys(const unsigned char* __restrict__ rgb,
-                                                       long long N, int n, unsigned* keys,
-                                                       unsigned* skey, int* counts) {
-    __shared__ int hist[kMaxBins];
-    for (int k = threadIdx.x; k < n; k += blockDim.x) hist[k] = 0;
+__global__ void __launch_bounds__(kSortThreads) k_hue_keys(const unsigned char* __restrict__ rgb,
+                                                           long long N, int n, int ntiles,
+                                                           float* hue, unsigned short* hilo, int* counts,
+                                                           int* lhist) {
+    extern __shared__ int hist[];              // [n], then [kLow]
+    int* const low = hist + n;
+    for (int k = threadIdx.x; k < n + kLow; k += kSortThreads) hist[k] = 0;
     __syncthreads();
-    const long long groups = (N + 3) / 4;
-    const long long stride = (long long)gridDim.x * blockDim.x;
-    for (long long gi = (long long)blockIdx.x * blockDim.x + threadIdx.x; gi < groups;
-         gi += stride) {
-        const long long p0 = 4 * gi;
+    const int tile = tile_of(blockIdx.x, ntiles);
+    const long long base = (long long)tile * kSortTile;
+    auto count = [&](float h) {
+        atomicAdd(&hist[bin_of(h, n)], 1);
+        atomicAdd(&low[sort_key(h) & (kLow - 1)], 1);
+    };
+#pragma unroll
+    for (int r = 0; r < kSortItems / 4; ++r) {
+        const long long p0 = base + 4 * (r * kSortThreads + (int)threadIdx.x);
         if (VEC && p0 + 4 <= N) {
             union { uint3 v; unsigned char b[12]; } in;
             in.v = *reinterpret_cast<const uint3*>(rgb + 3 * p0);
-            uint4 kv, sv;
-            unsigned* ku = reinterpret_cast<unsigned*>(&kv);
-            unsigned* su = reinterpret_cast<unsigned*>(&sv);
+            union { uint2 v; unsigned short u[4]; } m;
+            float h[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const Hue u = hue_of(in.b[3 * i], in.b[3 * i + 1], in.b[3 * i + 2]);
-                ku[i] = __float_as_uint(u.h);
-                su[i] = sort_key(u.h);
-                atomicAdd(&hist[bin_of(u.h, n)], 1);
+                h[i] = u.h;
+                m.u[i] = (unsigned short)(u.hi | u.lo << 8);
             }
-            *reinterpret_cast<uint4*>(keys + p0) = kv;
-            *reinterpret_cast<uint4*>(skey + p0) = sv;
+            *reinterpret_cast<float4*>(hue + p0) = make_float4(h[0], h[1], h[2], h[3]);
+            *reinterpret_cast<uint2*>(hilo + p0) = m.v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) count(h[i]);
         } else {
             for (long long p = p0; p < p0 + 4 && p < N; ++p) {
                 const unsigned char* c = rgb + 3 * p;
                 const Hue u = hue_of(c[0], c[1], c[2]);
-                keys[p] = __float_as_uint(u.h);
-                skey[p] = sort_key(u.h);
-                atomicAdd(&hist[bin_of(u.h, n)], 1);
+                hue[p] = u.h;
+                hilo[p] = (unsigned short)(u.hi | u.lo << 8);
+                count(u.h);
             }
         }
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < n; k += blockDim.x)
+    for (int k = threadIdx.x; k < n; k += kSortThreads)
         if (hist[k]) atomicAdd(&counts[k], hist[k]);
+    for (int d = threadIdx.x; d < kLow; d += kSortThreads) lhist[(long long)d * ntiles + tile] = low[d];
 }
 
-// ---- stable LSD radix sort of the 24-bit keys ------------------------------
-// Tile i holds keys [i T, (i + 1) T) of the current order, T = kSortTile;
-// thread t takes element r kSortThreads + t of its tile in round r, so the
-// order (round, wave, lane) is the tile's element order.
-
-// hist[d][tile] = number of keys of digit d in the tile.
-__global__ void __launch_bounds__(kSortThreads) k_sort_hist(const unsigned* __restrict__ keys,
-                                                            long long N, int shift, int ntiles,
-                                                            int* hist) {
-    __shared__ int cnt[kRadix];
-    const int t = threadIdx.x;
-    if (t < kRadix) cnt[t] = 0;
+// hist[d][tile] = number of elements of high digit d in the tile.  Eight
+// elements per 16-byte load (the digits' array is 16-byte aligned).
+__global__ void __launch_bounds__(kSortThreads) k_sort_hist(const unsigned short* __restrict__ dig,
+                                                            long long N, int ntiles, int* hist) {
+    __shared__ int cnt[kHigh];
+    for (int d = threadIdx.x; d < kHigh; d += kSortThreads) cnt[d] = 0;
     __syncthreads();
-    const long long base = (long long)blockIdx.x * kSortTile;
+    const int tile = tile_of(blockIdx.x, ntiles);
+    const long long base = (long long)tile * kSortTile;
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-        const long long e = base + r * kSortThreads + t;
-        if (e < N) atomicAdd(&cnt[(keys[e] >> shift) & (kRadix - 1)], 1);
+    for (int r = 0; r < kSortItems / 8; ++r) {
+        const long long e = base + 8 * (r * kSortThreads + (int)threadIdx.x);
+        if (e + 8 <= N) {
+            union { uint4 v; unsigned short u[8]; } x;
+            x.v = *reinterpret_cast<const uint4*>(dig + e);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) atomicAdd(&cnt[x.u[i]], 1);
+        } else {
+            for (long long q = e; q < e + 8 && q < N; ++q) atomicAdd(&cnt[dig[q]], 1);
+        }
     }
     __syncthreads();
-    if (t < kRadix) hist[(long long)t * ntiles + blockIdx.x] = cnt[t];
+    for (int d = threadIdx.x; d < kHigh; d += kSortThreads) hist[(long long)d * ntiles + tile] = cnt[d];
 }
 
 // Block d: exclusive prefix sums of hist[d][0..ntiles) in place (the start of
-// each tile's run of digit d among all keys of digit d) and totals[d].
-__global__ void __launch_bounds__(kRadix) k_sort_scan(int* hist, int ntiles, int* totals) {
-    __shared__ int part[kRadix];
+// each tile's run of digit d among all elements of digit d) and totals[d].
+constexpr int kScanThreads = 256;
+
+__global__ void __launch_bounds__(kScanThreads) k_sort_scan(int* hist, int ntiles, int* totals) {
+    __shared__ int part[kScanThreads];
     const int t = threadIdx.x;
     int* h = hist + (long long)blockIdx.x * ntiles;
-    const int per = (ntiles + kRadix - 1) / kRadix;
+    const int per = (ntiles + kScanThreads - 1) / kScanThreads;
     const int i0 = t * per, i1 = min(i0 + per, ntiles);
     int sum = 0;
     for (int i = i0; i < i1; ++i) sum += h[i];
     part[t] = sum;
     __syncthreads();
-    for (int off = 1; off < kRadix; off <<= 1) {       // inclusive scan of the parts
+    for (int off = 1; off < kScanThreads; off <<= 1) {       // inclusive scan of the parts
         const int v = t >= off ? part[t - off] : 0;
         __syncthreads();
         part[t] += v;
@@ -275,117 +307,193 @@ __global__ void __launch_bounds__(kRadix) k_sort_scan(int* hist, int ntiles, int
         h[i] = run;
         run += v;
     }
-    if (t == kRadix - 1) totals[blockIdx.x] = part[t];
+    if (t == kScanThreads - 1) totals[blockIdx.x] = part[t];
 }
 
-// Exclusive scan of v over the kRadix threads t < kRadix of the block (all
-// threads of the block call it); returns the value for t < kRadix.
-__device__ __forceinline__ int radix_scan(int v, int* sh) {
-    const int t = threadIdx.x;
-    if (t < kRadix) sh[t] = v;
-    __syncthreads();
-    for (int off = 1; off < kRadix; off <<= 1) {
-        const int a = (t < kRadix && t >= off) ? sh[t - off] : 0;
-        __syncthreads();
-        if (t < kRadix) sh[t] += a;
-        __syncthreads();
+// Exclusive scan over the block of D values per thread (thread t: entries D t
+// + q); sh: one word per wave.
+template <int D>
+__device__ __forceinline__ void block_scan(int (&v)[D], int* sh) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int own = 0;
+#pragma unroll
+    for (int q = 0; q < D; ++q) own += v[q];
+    int inc = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int a = __shfl_up(inc, off, 64);
+        inc += lane >= off ? a : 0;
     }
-    const int r = t < kRadix ? sh[t] - v : 0;
+    __syncthreads();                           // (sh may still be read from a scan before)
+    if (lane == 63) sh[w] = inc;
     __syncthreads();
-    return r;
+    int run = inc - own;
+    for (int q = 0; q < w; ++q) run += sh[q];
+#pragma unroll
+    for (int q = 0; q < D; ++q) {
+        const int a = v[q];
+        v[q] = run;
+        run += a;
+    }
 }
 
-// One radix pass: every key goes to position off[d] + pre[d][tile] + (its
-// stable rank among the tile's keys of digit d), off[d] the number of keys of
-// smaller digits.  FIRST: the input index is the element's own position (the
-// raster index); LAST: writes rank_out[index] = position instead of the
-// sorted keys and indices.
-template <bool FIRST, bool LAST>
-__global__ void __launch_bounds__(kSortThreads) k_sort_scatter(
-    const unsigned* __restrict__ kin, const unsigned* __restrict__ iin, unsigned* kout,
-    unsigned* iout, unsigned* rank_out, long long N, int shift, int ntiles,
-    const int* __restrict__ pre, const int* __restrict__ totals) {
-    __shared__ int cnt[kSortWaves][kRadix];
-    __shared__ int run[kRadix], dbase[kRadix], dstart[kRadix], sh[kRadix];
-    __shared__ unsigned sk[kSortTile], si[kSortTile];
-    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
-    const long long tile = blockIdx.x, base = tile * kSortTile;
-    // global start of this tile's run of each digit
-    {
-        const int tot = t < kRadix ? totals[t] : 0;
-        const int off = radix_scan(tot, sh);
-        if (t < kRadix) {
-            dbase[t] = off + pre[(long long)t * ntiles + tile];
-            run[t] = 0;
-        }
-    }
-    unsigned key[kSortItems], idx[kSortItems];
-    int rk[kSortItems];
+// The rank of each of the wave's elements among the wave's earlier elements of
+// the same digit (rk), and the wave's counts of the digits in cnt (zeros on
+// entry).  valid holds for a prefix of the elements.
+template <int BITS>
+__device__ __forceinline__ void wave_ranks(const int (&dig)[kSortItems], const bool (&valid)[kSortItems],
+                                           int* cnt, int (&rk)[kSortItems]) {
+    const unsigned long long lt = (1ull << (threadIdx.x & 63)) - 1ull;
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {
-        const long long e = base + r * kSortThreads + t;
-        const bool valid = e < N;
-        key[r] = valid ? kin[e] : 0u;
-        idx[r] = valid ? (FIRST ? (unsigned)e : iin[e]) : 0u;
-    }
-    const unsigned long long lt = (1ull << lane) - 1ull;
-    for (int r = 0; r < kSortItems; ++r) {
-        for (int i = t; i < kSortWaves * kRadix; i += kSortThreads) (&cnt[0][0])[i] = 0;
-        __syncthreads();
-        const bool valid = base + r * kSortThreads + t < N;
-        const int d = (int)((key[r] >> shift) & (kRadix - 1));
-        // lanes of this wave with the same digit
-        unsigned long long peers = __ballot(valid);
+        unsigned long long peers = __ballot(valid[r]);      // lanes of the same digit
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const bool bit = (d >> b) & 1;
-            const unsigned long long m = __ballot(valid && bit);
+        for (int b = 0; b < BITS; ++b) {
+            const bool bit = (dig[r] >> b) & 1;
+            const unsigned long long m = __ballot(bit);
             peers &= bit ? m : ~m;
         }
         const int lr = __popcll(peers & lt);
-        if (valid && lr == 0) cnt[w][d] = __popcll(peers);
-        __syncthreads();
-        if (t < kRadix) {          // digit t: start of each wave's keys in this round
-            int s0 = run[t];
-#pragma unroll
-            for (int q = 0; q < kSortWaves; ++q) {
-                const int c = cnt[q][t];
-                cnt[q][t] = s0;
-                s0 += c;
-            }
-            run[t] = s0;
-        }
-        __syncthreads();
-        rk[r] = valid ? cnt[w][d] + lr : 0;
-        __syncthreads();
+        const int before = cnt[dig[r]];
+        rk[r] = before + lr;
+        if (valid[r] && lr == 0) cnt[dig[r]] = before + __popcll(peers);
+        // the next round's loads see this round's stores (one wave's LDS
+        // operations complete in order)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    // the tile sorted by digit in LDS: digit runs in order, each stable
-    {
-        const int st = radix_scan(t < kRadix ? run[t] : 0, sh);
-        if (t < kRadix) dstart[t] = st;
+}
+
+__global__ void __launch_bounds__(kSortThreads) k_sort_low(const float* __restrict__ hue, long long N,
+                                                           int ntiles, const int* __restrict__ pre,
+                                                           const int* __restrict__ totals,
+                                                           unsigned* pos, unsigned short* high) {
+    static_assert(kLow == kSortThreads, "a thread per digit");
+    __shared__ int cnt[kSortWaves][kLow];      // counts, then in-tile starts, per wave and digit
+    __shared__ int gbase[kLow];                // a digit's place in the tile to its global place
+    __shared__ int sh[kSortWaves];
+    __shared__ unsigned st[kSortTile];         // the tile in order: keys
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+    const int tile = tile_of(blockIdx.x, ntiles);
+    const long long base = (long long)tile * kSortTile;
+    int off[1] = {totals[t]};
+    const int first = pre[(long long)t * ntiles + tile];
+    int dig[kSortItems], rk[kSortItems];
+    unsigned key[kSortItems];
+    bool valid[kSortItems];
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r) {
+        const long long e = base + w * (kSortTile / kSortWaves) + r * 64 + lane;
+        valid[r] = e < N;
+        key[r] = sort_key(hue[valid[r] ? e : 0]);
+        dig[r] = key[r] & (kLow - 1);
+    }
+    for (int i = t; i < kSortWaves * kLow; i += kSortThreads) (&cnt[0][0])[i] = 0;
+    block_scan(off, sh);                       // (its barriers order the zeros)
+    wave_ranks<kLowBits>(dig, valid, cnt[w], rk);
+    __syncthreads();
+    {   // digit t
+        int run[1] = {0}, c[kSortWaves];
+#pragma unroll
+        for (int q = 0; q < kSortWaves; ++q) {
+            c[q] = cnt[q][t];
+            run[0] += c[q];
+        }
+        block_scan(run, sh);                   // the digit's start in the tile
+        gbase[t] = off[0] + first - run[0];
+        int s0 = run[0];
+#pragma unroll
+        for (int q = 0; q < kSortWaves; ++q) {
+            cnt[q][t] = s0;
+            s0 += c[q];
+        }
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {
-        if (base + r * kSortThreads + t < N) {
-            const int d = (int)((key[r] >> shift) & (kRadix - 1));
-            const int p = dstart[d] + rk[r];
-            sk[p] = key[r];
-            si[p] = idx[r];
-        }
+        if (!valid[r]) continue;
+        const int p = cnt[w][dig[r]] + rk[r];
+        st[p] = key[r];
+        pos[base + w * (kSortTile / kSortWaves) + r * 64 + lane] = gbase[dig[r]] + p;
     }
     __syncthreads();
     const int nh = (int)min((long long)kSortTile, N - base);
-    for (int j = t; j < nh; j += kSortThreads) {
-        const unsigned k = sk[j];
-        const int d = (int)((k >> shift) & (kRadix - 1));
-        const long long pos = (long long)dbase[d] + (j - dstart[d]);
-        if (LAST) {
-            rank_out[si[j]] = (unsigned)pos;
-        } else {
-            kout[pos] = k;
-            iout[pos] = si[j];
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r) {
+        const int j = r * kSortThreads + t;
+        if (j >= nh) continue;
+        const unsigned k = st[j];
+        high[gbase[k & (kLow - 1)] + j] = (unsigned short)(k >> kLowBits);
+    }
+}
+
+__global__ void __launch_bounds__(kSortThreads) k_sort_high(const unsigned short* __restrict__ high,
+                                                            long long N, int ntiles,
+                                                            const int* __restrict__ pre,
+                                                            const int* __restrict__ totals,
+                                                            unsigned* rank) {
+    constexpr int D = kHigh / kSortThreads;    // digits per thread
+    static_assert(D * kSortThreads == kHigh, "whole digits per thread");
+    __shared__ int cnt[kSortWaves][kHigh];     // counts, then global starts, per wave and digit
+    __shared__ int sh[kSortWaves];
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+    const int tile = tile_of(blockIdx.x, ntiles);
+    const long long base = (long long)tile * kSortTile + w * (kSortTile / kSortWaves) + lane;
+    int off[D], first[D];
+#pragma unroll
+    for (int q = 0; q < D; ++q) {
+        off[q] = totals[D * t + q];
+        first[q] = pre[(long long)(D * t + q) * ntiles + tile];
+    }
+    int dig[kSortItems], rk[kSortItems];
+    bool valid[kSortItems];
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r) {
+        valid[r] = base + r * 64 < N;
+        dig[r] = high[valid[r] ? base + r * 64 : 0];
+    }
+    for (int i = t; i < kSortWaves * kHigh; i += kSortThreads) (&cnt[0][0])[i] = 0;
+    block_scan(off, sh);                       // (its barriers order the zeros)
+    wave_ranks<kKeyBits - kLowBits>(dig, valid, cnt[w], rk);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < D; ++q) {
+        int s0 = off[q] + first[q];
+#pragma unroll
+        for (int i = 0; i < kSortWaves; ++i) {
+            const int c = cnt[i][D * t + q];
+            cnt[i][D * t + q] = s0;
+            s0 += c;
         }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r)
+        if (valid[r]) rank[base + r * 64] = (unsigned)(cnt[w][dig[r]] + rk[r]);
+}
+
+// rank[p] = ranks[pos[p]], four pixels per thread and step (16-byte accesses): a
+// tile's reads of ranks are its runs of equal low digits.
+__global__ void __launch_bounds__(kSortThreads) k_sort_gather(const unsigned* __restrict__ pos,
+                                                              const unsigned* __restrict__ ranks,
+                                                              long long N, int ntiles, unsigned* rank) {
+    const long long base = (long long)tile_of(blockIdx.x, ntiles) * kSortTile + 4 * threadIdx.x;
+    if ((long long)(tile_of(blockIdx.x, ntiles) + 1) * kSortTile <= N) {
+        constexpr int Q = kSortItems / 4;
+        union { uint4 v; unsigned u[4]; } p[Q], o[Q];
+#pragma unroll
+        for (int r = 0; r < Q; ++r) p[r].v = *reinterpret_cast<const uint4*>(pos + base + 4 * r * kSortThreads);
+#pragma unroll
+        for (int r = 0; r < Q; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[r].u[i] = ranks[p[r].u[i]];
+#pragma unroll
+        for (int r = 0; r < Q; ++r) *reinterpret_cast<uint4*>(rank + base + 4 * r * kSortThreads) = o[r].v;
+    } else {
+        for (int r = 0; r < kSortItems / 4; ++r)
+            for (long long e = base + 4 * r * kSortThreads, i = 0; i < 4 && e + i < N; ++i)
+                rank[e + i] = ranks[pos[e + i]];
     }
 }
 
@@ -557,28 +665,27 @@ __device__ __forceinline__ void out_bins(const unsigned* rk, int s, int N, const
     for (int i = 0; i < W; ++i) lo[i] = min(lo[i] + (cl[lo[i]] <= q[i] ? 1 : 0), n - 1);
 }
 
-// One pixel of a frame: its hue h (the source's sort key, computed once per
-// source) moved to the output bin, RGB rebuilt with the max and min channels.
-__device__ __forceinline__ void paint_px(const unsigned char* c, float h, int kout, int n,
+// One pixel of a frame: its hue h (computed once per source) moved to the output
+// bin, RGB rebuilt with the max and min channels (hilo).
+__device__ __forceinline__ void paint_px(unsigned short hilo, float h, int kout, int n,
                                          unsigned char* o) {
 #pragma clang fp contract(off)
-    const int r = c[0], g = c[1], b = c[2];
     const int ksrc = bin_of(h, n);
     float h2 = h + (float)(kout - ksrc) / (float)n;
     if (h2 >= 1.f) h2 = h2 - 1.f;
     if (h2 < 0.f) h2 = h2 + 1.f;
     if (h2 >= 1.f) h2 = h2 - 1.f;
-    rgb_of(h2, max(max(r, g), b), min(min(r, g), b), o);
+    rgb_of(h2, hilo & 255, hilo >> 8, o);
 }
 
 // One frame over the pixels in raster order, four pixels per thread in a
-// grid-stride loop.  VEC: the image pointers are 4-byte aligned (and bins_out
-// 16-byte aligned), so a group of four moves as 12 bytes of RGB, 16 bytes of
-// rank and 16 bytes of bins; the tail group and unaligned images go pixel by
+// grid-stride loop.  VEC: the output is 4-byte aligned (and bins_out 16-byte
+// aligned), so a group of four moves as 12 bytes of RGB, 8 bytes of max and min
+// channels, 16 bytes each of hue, rank and bins; the tail group and unaligned images go pixel by
 // pixel.
 template <bool VEC>
-__global__ void __launch_bounds__(kThreads) k_hue_render(const unsigned char* __restrict__ rgb,
-                                                         const unsigned* __restrict__ hue,
+__global__ void __launch_bounds__(kThreads) k_hue_render(const unsigned short* __restrict__ hilo,
+                                                         const float* __restrict__ hue,
                                                          const unsigned* __restrict__ rank,
                                                          const int* __restrict__ cum,
                                                          const long long* __restrict__ shift,
@@ -602,16 +709,18 @@ __global__ void __launch_bounds__(kThreads) k_hue_render(const unsigned char* __
          gi += stride) {
         const long long p0 = 4 * gi;
         if (VEC && p0 + 4 <= N) {
-            union { uint3 v; unsigned char b[12]; } in, o;
-            union { uint4 v; unsigned u[4]; } rk, hu;
-            in.v = *reinterpret_cast<const uint3*>(rgb + 3 * p0);
+            union { uint3 v; unsigned char b[12]; } o;
+            union { uint2 v; unsigned short u[4]; } m;
+            union { uint4 v; unsigned u[4]; } rk;
+            m.v = *reinterpret_cast<const uint2*>(hilo + p0);
             rk.v = *reinterpret_cast<const uint4*>(rank + p0);
-            hu.v = *reinterpret_cast<const uint4*>(hue + p0);
+            const float4 hu = *reinterpret_cast<const float4*>(hue + p0);
+            const float hv[4] = {hu.x, hu.y, hu.z, hu.w};
             int kb[4];
             out_bins<4>(rk.u, s32, N32, cl, n, pw, kb);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                paint_px(in.b + 3 * i, __uint_as_float(hu.u[i]), kb[i], n, o.b + 3 * i);
+                paint_px(m.u[i], hv[i], kb[i], n, o.b + 3 * i);
             *reinterpret_cast<uint3*>(out + 3 * p0) = o.v;
             if (bins_out) *reinterpret_cast<int4*>(bins_out + p0) = make_int4(kb[0], kb[1], kb[2], kb[3]);
         } else {
@@ -619,7 +728,7 @@ __global__ void __launch_bounds__(kThreads) k_hue_render(const unsigned char* __
                 const unsigned r1 = rank[p];
                 int k;
                 out_bins<1>(&r1, s32, N32, cl, n, pw, &k);
-                paint_px(rgb + 3 * p, __uint_as_float(hue[p]), k, n, out + 3 * p);
+                paint_px(hilo[p], hue[p], k, n, out + 3 * p);
                 if (bins_out) bins_out[p] = k;
             }
         }
@@ -630,7 +739,7 @@ unsigned blocks_for(long long n, int t) { return (unsigned)((n + t - 1) / t); }
 
 // Workspace carve of a renderer (256-byte aligned pieces).
 struct HueLayout {
-    size_t keys, skey, skey2, idxa, idxb, hist, totals, counts, ct, cum, shift, total;
+    size_t hue, hilo, high, pos, ranks, rank, hist, totals, counts, ct, cum, shift, total;
     int ntiles;
 };
 
@@ -640,13 +749,14 @@ HueLayout hue_layout(long long N, int n, int frames) {
     auto take = [&](size_t bytes) { size_t r = o; o = (o + bytes + 255) / 256 * 256; return r; };
     const size_t w = (size_t)N * sizeof(unsigned);
     L.ntiles = (int)((N + kSortTile - 1) / kSortTile);
-    L.keys = take(w);
-    L.skey = take(w);
-    L.skey2 = take(w);
-    L.idxa = take(w);
-    L.idxb = take(w);
-    L.hist = take((size_t)kRadix * L.ntiles * sizeof(int));
-    L.totals = take(kRadix * sizeof(int));
+    L.hue = take(w);
+    L.hilo = take((size_t)N * sizeof(unsigned short));
+    L.pos = take(w);
+    L.high = take((size_t)N * sizeof(unsigned short));
+    L.ranks = take(w);
+    L.rank = take(w);
+    L.hist = take((size_t)kHigh * L.ntiles * sizeof(int));
+    L.totals = take(kHigh * sizeof(int));
     L.counts = take((size_t)n * sizeof(int));
     L.ct = take((size_t)frames * n * sizeof(int));
     L.cum = take((size_t)frames * n * sizeof(int));
@@ -670,15 +780,15 @@ struct ot_hue {
     int cap = 0;                        // frames the plan arrays hold
     int ntiles = 0;
     hipStream_t st = nullptr;
-    // keys: each pixel's hue (FP32 bits, raster order, read by the frames);
-    // skey/skey2: 24-bit sort keys, idxa/idxb: the sort's raster indices
-    // (idxb holds the ranks once the sort is done)
-    unsigned *keys = nullptr, *skey = nullptr, *skey2 = nullptr, *idxa = nullptr, *idxb = nullptr;
-    unsigned* rank = nullptr;
+    // hue, hilo, rank: each pixel's hue, max and min channel and rank (raster
+    // order, read by the frames); pos: its position in the order of the low
+    // digit; high, ranks: the high digits and ranks in that order
+    float* hue = nullptr;
+    unsigned short *hilo = nullptr, *high = nullptr;
+    unsigned *pos = nullptr, *ranks = nullptr, *rank = nullptr;
     int *hist = nullptr, *totals = nullptr;
     int *counts = nullptr, *ct = nullptr, *cum = nullptr;
     long long* shift = nullptr;
-    const unsigned char* src = nullptr;
     bool have_source = false;
     int planned = 0;                    // frames of the last plan (0: none)
 };
@@ -709,12 +819,12 @@ int ot_hue_create(long long npix, int nbins, int max_frames, void* stream, void*
     h->cap = max_frames;
     h->ntiles = L.ntiles;
     h->st = (hipStream_t)stream;
-    h->keys = (unsigned*)(ws + L.keys);
-    h->skey = (unsigned*)(ws + L.skey);
-    h->skey2 = (unsigned*)(ws + L.skey2);
-    h->idxa = (unsigned*)(ws + L.idxa);
-    h->idxb = (unsigned*)(ws + L.idxb);
-    h->rank = h->idxb;
+    h->hue = (float*)(ws + L.hue);
+    h->hilo = (unsigned short*)(ws + L.hilo);
+    h->pos = (unsigned*)(ws + L.pos);
+    h->high = (unsigned short*)(ws + L.high);
+    h->ranks = (unsigned*)(ws + L.ranks);
+    h->rank = (unsigned*)(ws + L.rank);
     h->hist = (int*)(ws + L.hist);
     h->totals = (int*)(ws + L.totals);
     h->counts = (int*)(ws + L.counts);
@@ -735,44 +845,27 @@ int ot_hue_set_source(ot_hue* h, const unsigned char* rgb) {
     if (!h || !rgb) return OT_ERR_PARAM;
     hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(h->n, kThreads)), dim3(kThreads), 0, h->st,
                        h->counts, h->n, 0);
-    const unsigned kb = blocks_for((h->N + 3) / 4, kThreads);
-    const dim3 kgrid(kb < kKeyBlocks ? kb : kKeyBlocks);
+    const dim3 tiles(h->ntiles), block(kSortThreads);
+    const size_t lds = (size_t)(h->n + kLow) * sizeof(int);
     if ((uintptr_t)rgb % 4 == 0)
-        hipLaunchKernelGGL(k_hue_keys<true>, kgrid, dim3(kThreads), 0, h->st, rgb, h->N, h->n,
-                           h->keys, h->skey, h->counts);
+        hipLaunchKernelGGL(k_hue_keys<true>, tiles, block, lds, h->st, rgb, h->N, h->n, h->ntiles,
+                           h->hue, h->hilo, h->counts, h->hist);
     else
-        hipLaunchKernelGGL(k_hue_keys<false>, kgrid, dim3(kThreads), 0, h->st, rgb, h->N, h->n,
-                           h->keys, h->skey, h->counts);
-    // stable radix sort of the 24-bit keys (sort_key): equal hues keep raster
-    // order.  Pass 0: keys skey -> skey2, raster indices (implicit) -> idxb;
-    // pass 1: skey2 -> skey, idxb -> idxa; pass 2 reads skey and idxa and
-    // writes each pixel's rank into idxb.
-    const unsigned* kin[3] = {h->skey, h->skey2, h->skey};
-    unsigned* kout[3] = {h->skey2, h->skey, nullptr};
-    const unsigned* iin[3] = {nullptr, h->idxb, h->idxa};
-    unsigned* iout[3] = {h->idxb, h->idxa, nullptr};
-    for (int pass = 0; pass < kKeyBits / 8; ++pass) {
-        const int shift = 8 * pass;
-        hipLaunchKernelGGL(k_sort_hist, dim3(h->ntiles), dim3(kSortThreads), 0, h->st, kin[pass],
-                           h->N, shift, h->ntiles, h->hist);
-        hipLaunchKernelGGL(k_sort_scan, dim3(kRadix), dim3(kRadix), 0, h->st, h->hist, h->ntiles,
-                           h->totals);
-        if (pass == 0)
-            hipLaunchKernelGGL((k_sort_scatter<true, false>), dim3(h->ntiles), dim3(kSortThreads), 0,
-                               h->st, kin[0], nullptr, kout[0], iout[0], nullptr, h->N, shift,
-                               h->ntiles, h->hist, h->totals);
-        else if (pass == 1)
-            hipLaunchKernelGGL((k_sort_scatter<false, false>), dim3(h->ntiles), dim3(kSortThreads),
-                               0, h->st, kin[1], iin[1], kout[1], iout[1], nullptr, h->N, shift,
-                               h->ntiles, h->hist, h->totals);
-        else
-            hipLaunchKernelGGL((k_sort_scatter<false, true>), dim3(h->ntiles), dim3(kSortThreads),
-                               0, h->st, kin[2], iin[2], nullptr, nullptr, h->idxb, h->N, shift,
-                               h->ntiles, h->hist, h->totals);
-    }
+        hipLaunchKernelGGL(k_hue_keys<false>, tiles, block, lds, h->st, rgb, h->N, h->n, h->ntiles,
+                           h->hue, h->hilo, h->counts, h->hist);
+    // stable radix sort of the keys (sort_key): equal hues keep raster order
+    hipLaunchKernelGGL(k_sort_scan, dim3(kLow), dim3(kScanThreads), 0, h->st, h->hist, h->ntiles,
+                       h->totals);
+    hipLaunchKernelGGL(k_sort_low, tiles, block, 0, h->st, h->hue, h->N, h->ntiles, h->hist,
+                       h->totals, h->pos, h->high);
+    hipLaunchKernelGGL(k_sort_hist, tiles, block, 0, h->st, h->high, h->N, h->ntiles, h->hist);
+    hipLaunchKernelGGL(k_sort_scan, dim3(kHigh), dim3(kScanThreads), 0, h->st, h->hist, h->ntiles,
+                       h->totals);
+    hipLaunchKernelGGL(k_sort_high, tiles, block, 0, h->st, h->high, h->N, h->ntiles, h->hist,
+                       h->totals, h->ranks);
+    hipLaunchKernelGGL(k_sort_gather, tiles, block, 0, h->st, h->pos, h->ranks, h->N,
+                       h->ntiles, h->rank);
     if (hipGetLastError() != hipSuccess) return OT_ERR_HIP;
-    h->rank = h->idxb;
-    h->src = rgb;
     h->have_source = true;
     h->planned = 0;
     return OT_OK;
@@ -812,17 +905,17 @@ int ot_hue_apply(ot_hue* h, unsigned char* rgb_out, int* bins_out) {
     const unsigned gb = blocks_for((h->N + 3) / 4, kThreads);
     const dim3 grid(gb < kRenderBlocks ? gb : kRenderBlocks, (unsigned)F);
     // every frame's image 4-byte aligned and bins 16-byte aligned
-    const bool vec = ((uintptr_t)h->src % 4 == 0) && ((uintptr_t)rgb_out % 4 == 0) &&
+    const bool vec = ((uintptr_t)rgb_out % 4 == 0) &&
                      ((uintptr_t)bins_out % 16 == 0) &&
                      (F == 1 || ((3 * h->N) % 4 == 0 && (!bins_out || h->N % 4 == 0)));
     // LDS: the cumulative counts padded to the next power of two (<= 16 KB)
     const size_t lds = sizeof(int) * (h->n > 1 ? (size_t)1 << (32 - __builtin_clz(h->n - 1)) : 1);
     if (vec)
-        hipLaunchKernelGGL(k_hue_render<true>, grid, dim3(kThreads), lds, h->st, h->src, h->keys,
+        hipLaunchKernelGGL(k_hue_render<true>, grid, dim3(kThreads), lds, h->st, h->hilo, h->hue,
                            h->rank,
                            h->cum, h->shift, h->n, h->N, rgb_out, bins_out);
     else
-        hipLaunchKernelGGL(k_hue_render<false>, grid, dim3(kThreads), lds, h->st, h->src, h->keys,
+        hipLaunchKernelGGL(k_hue_render<false>, grid, dim3(kThreads), lds, h->st, h->hilo, h->hue,
                            h->rank,
                            h->cum, h->shift, h->n, h->N, rgb_out, bins_out);
     return hipGetLastError() == hipSuccess ? OT_OK : OT_ERR_HIP;
