@@ -368,11 +368,12 @@ def hue_render(args):
     dt = time.perf_counter() - t0
     apply_us = 1e3 * sum(a.elapsed_time(b) for a, b in ev) / K
     r.close()
-    nbytes = 13.0 * N * F             # read channels (2) + hue (4) + rank (4), write RGB (3), per frame
+    # read channels (2) + hue (4) + rank (4) once per four frames, write RGB (3)
+    nbytes = N * (10.0 * ((F + 3) // 4) + 3.0 * F)
     from paper_1501_04840_amd import profile_traffic
     traffic = None
     if (H, W, n, F) == (2160, 3840, 360, 33):      # the counted workload
-        traffic = measured_traffic("k_hue_render<true>", "traffic_hue.json",
+        traffic = measured_traffic("k_hue_render<true, 9, 4>", "traffic_hue.json",
                                    profile_traffic.hue_sources_hash())
     achieved = nbytes / (apply_us * 1e-6) / 1e9
     out_json = {
