@@ -187,8 +187,7 @@ int build_graph(ot_dyn_batch* bt, int chunk) {
         varies = varies || plan_launch_varies(g.plan);
         e = hipStreamWaitEvent(g.side, bt->ev_fork, 0);
         if (e != hipSuccess) break;
-        for (int it = 0; it < chunk; ++it)
-            plan_iterate(g.plan, g.F, g.Mx, g.My, g.Mc, it + 1 == chunk);
+        plan_iterate(g.plan, g.F, g.Mx, g.My, g.Mc, chunk, true);
         e = hipEventRecord(bt->ev_join[act[i]], g.side);
         if (e == hipSuccess) e = hipStreamWaitEvent(bt->stream, bt->ev_join[act[i]], 0);
     }
@@ -353,9 +352,9 @@ int ot_dyn_batch_autotune(ot_dyn_batch* bt, int trials) {
                 plan_apply_tuning(g.plan, bx, dn);
                 int st = ot_dyn_init(g.plan, OT_INIT_COLD, g.F, g.Mx, g.My, g.Mc);
                 if (st != OT_OK) { status = st; break; }
-                for (int w = 0; w < 2; ++w) plan_iterate(g.plan, g.F, g.Mx, g.My, g.Mc, false);
+                plan_iterate(g.plan, g.F, g.Mx, g.My, g.Mc, 2, false);
                 if (hipEventRecord(t0, g.side) != hipSuccess) { status = OT_ERR_HIP; break; }
-                for (int w = 0; w < trials; ++w) plan_iterate(g.plan, g.F, g.Mx, g.My, g.Mc, false);
+                plan_iterate(g.plan, g.F, g.Mx, g.My, g.Mc, trials, false);
                 if (hipEventRecord(t1, g.side) != hipSuccess ||
                     hipEventSynchronize(t1) != hipSuccess) { status = OT_ERR_HIP; break; }
                 float ms = 0.f;

@@ -168,9 +168,10 @@ __device__ __forceinline__ void line_dct2(float* s, int t, const float2* tw4, bo
 
 // Orthonormal DCT-III (inverse of line_dct2) in place.  BLOCK_END false: end
 // with a wavefront sync only, for callers that afterwards read nothing but
-// the lines of their own wavefront.
+// the lines of their own wavefront.  Threads with `act` false only take part in
+// the synchronisation.
 template <int M1, int M2, int XP = 0, bool BLOCK_END = true>
-__device__ __forceinline__ void line_dct3(float* s, int t, const float2* tw4) {
+__device__ __forceinline__ void line_dct3(float* s, int t, const float2* tw4, bool act = true) {
     constexpr int M = M1 * M2, L = 2 * M, T = M2, NP = (M / 2 + T) / T;
     // inputs scaled by sqrt(L / 2) (sqrt(L) for X[0]); with V(k) =
     // conj(w4_k) (X[k], -X[L-k]), the packed spectrum is
@@ -183,7 +184,7 @@ __device__ __forceinline__ void line_dct3(float* s, int t, const float2* tw4) {
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
         const int k = t + T * j;
-        if (k <= M / 2) {
+        if (act && k <= M / 2) {
             const float xk = k == 0 ? 1.41421356237309515f * s[0] : ip[T * j];
             const float xl = j == 0 ? (k == 0 ? 0.f : s[L - t]) : im_[L - T * j];   // X[L-k]
             const float xm = im_[M - T * j];                                         // X[M-k]
@@ -200,7 +201,7 @@ __device__ __forceinline__ void line_dct3(float* s, int t, const float2* tw4) {
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
         const int k = t + T * j;
-        if (k <= M / 2) {
+        if (act && k <= M / 2) {
             st2(s + 2 * t, T * j, zc[j][0]);
             if (k > 0 && k < M / 2) st2(s - 2 * t, M - T * j, zc[j][1]);
         }
@@ -208,7 +209,7 @@ __device__ __forceinline__ void line_dct3(float* s, int t, const float2* tw4) {
     line_sync();
     float2 r[M1 / M2][M2];
     const float* const sl = s + 2 * t;
-    fft_core<M1, M2, XP>(s, t, tw4, [&](int n1) { return ld2(sl, M2 * n1); }, r);
+    fft_core<M1, M2, XP>(s, t, tw4, [&](int n1) { return ld2(sl, M2 * n1); }, r, act);
     line_sync();
     // output n = t + M2 q + M1 k2: x[pos(2n)] = Re r / M, x[pos(2n+1)] = -Im r / M
     // with pos(m) = 2m (m < M), 2(L-1-m)+1 (m >= M); m < M iff the
@@ -221,6 +222,7 @@ __device__ __forceinline__ void line_dct3(float* s, int t, const float2* tw4) {
 #pragma unroll
         for (int k2 = 0; k2 < M2; ++k2) {
             const int B = 2 * (M2 * q + M1 * k2);
+            if (!act) continue;
             if (B < M) {
                 wp[2 * B] = r[q][k2].x * sc;
                 wp[2 * B + 2] = -r[q][k2].y * sc;
@@ -487,12 +489,12 @@ __device__ __forceinline__ void line_xform_mix(float* s, int t, const float2* tw
 // XP: exchange padding of the DCTs (fft_core); the line's LDS region then
 // needs max(2 M, M1 (2 M2 + XP)) floats.
 template <int M1, int M2, int KIND, int XP = 0, bool BLOCK_END = true>
-__device__ __forceinline__ void line_xform(float* s, int t, const float2* tw4) {
+__device__ __forceinline__ void line_xform(float* s, int t, const float2* tw4, bool act = true) {
     static_assert(KIND != 2 || XP == 0, "no padded exchange for the Hartley transform");
     static_assert(BLOCK_END || KIND == 1, "a wavefront-sync end only for the DCT-III");
-    if constexpr (KIND == 0) line_dct2<M1, M2, XP>(s, t, tw4);
-    else if constexpr (KIND == 1) line_dct3<M1, M2, XP, BLOCK_END>(s, t, tw4);
-    else line_dht<M1, M2>(s, t, tw4);
+    if constexpr (KIND == 0) line_dct2<M1, M2, XP>(s, t, tw4, act);
+    else if constexpr (KIND == 1) line_dct3<M1, M2, XP, BLOCK_END>(s, t, tw4, act);
+    else line_dht<M1, M2>(s, t, tw4, act);
 }
 
 }  // namespace otd

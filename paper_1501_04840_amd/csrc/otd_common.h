@@ -253,6 +253,13 @@ bool poisson_1d_ok(const Geom& g, const AxisTab& tx, const AxisTab& tt);
 void launch_poisson_1d(const Geom& g, float* R, const AxisTab& tx, const AxisTab& ty,
                        const AxisTab& tc, const AxisTab& tt, const double* tc64,
                        const double* tt64, const float* frz, hipStream_t st);
+// Whole iterations of such problems with the carried potential and without a
+// residual check, in one launch: the first `refined` of `iters` with the
+// refinement solve.  ok: fast transforms along x, Neumann y, aligned fields.
+bool iterations_1d_ok(const StepArgs& s, const AxisTab& tx, const AxisTab& tt);
+void launch_iterations_1d(const StepArgs& s, const AxisTab& tx, const AxisTab& ty, const AxisTab& tc,
+                          const AxisTab& tt, const double* tc64, const double* tt64, int iters,
+                          int refined, hipStream_t st);
 
 // Fast power-of-two passes (fastdct.hip); kind 0 DCT-II, 1 DCT-III, 2 Hartley.
 bool fast_len(int L);
@@ -271,7 +278,8 @@ void launch_cols_fast(float* R, long long outer, long long inner, int L, const f
 struct ot_dyn_plan;
 struct ot_dyn_report;
 namespace otd {
-void plan_iterate(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc, bool check);
+// `iters` iterations, the last with residual partials when `check`.
+void plan_iterate(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc, int iters, bool check);
 int plan_collect(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc);
 void plan_apply_tuning(ot_dyn_plan* p, int row_bx, int dense_xy);
 bool plan_has_fast_xy(const ot_dyn_plan* p);

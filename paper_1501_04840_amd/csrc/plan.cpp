@@ -212,7 +212,8 @@ Layout layout_of(const ot_dyn_desc& d) {
     L.off_dense[0] = take(dense ? dense_axis_floats(d.X, g.perx) * sizeof(float) : 0);
     L.off_dense[1] = take(dense ? dense_axis_floats(d.Y, g.pery) * sizeof(float) : 0);
     L.off_tc64 = take(((size_t)d.C * d.C + d.C) * sizeof(double));
-    L.off_tt64 = take(((size_t)d.P * d.P + d.P) * sizeof(double));
+    const size_t dc = d.Y == 1 && d.C == 1 && d.P <= 32 ? (size_t)d.P * d.P : 0;    // dc_table_1d
+    L.off_tt64 = take(((size_t)d.P * d.P + d.P + dc) * sizeof(double));
     // FP64 partials: per-node kernels write one per 256 nodes of a plane; the
     // row kernels one per row segment and colour (plane stride Y * nxb)
     L.nbx_node = (int)((g.plane + 255) / 256);
@@ -270,6 +271,19 @@ void axis_eigs(int n, int periodic, double s, std::vector<double>& lam) {
         const double sn = std::sin(pi * j / (periodic ? n : 2.0 * n));
         lam[j] = 4.0 * s * s * sn * sn;
     }
+}
+
+// The spatial-DC line of a problem with one spatial axis as one product of its
+// row sums: D = M^T diag(1 / lam) M / sqrt(X) (the zero mode dropped), appended.
+void dc_table_1d(int n, int X, const std::vector<double>& M, const std::vector<double>& lam,
+                 std::vector<double>& out) {
+    for (int k = 0; k < n; ++k)
+        for (int t = 0; t < n; ++t) {
+            double s = 0.0;
+            for (int j = 0; j < n; ++j)
+                if (lam[j] > 0.0) s += M[(size_t)j * n + k] * M[(size_t)j * n + t] / lam[j];
+            out.push_back(s / std::sqrt((double)X));
+        }
 }
 
 int hip_fail(ot_dyn_plan* p, hipError_t e, const char* what) {
@@ -467,6 +481,29 @@ void iterate(ot_dyn_plan* p, const StepArgs& s, bool check) {
     }
     // x = a + grad phi_1 (+ grad phi_2); prox; duals
     timed(p, OT_PHASE_UPDATE, [&] { launch_update(s, check ? 1 : 0, refine ? 2 : 1, st); });
+}
+
+// `iters` iterations of Algorithm 1 without a residual check: whole ones in one
+// launch where a block can own a problem (launches of at most kRunIters
+// iterations, milliseconds), else one by one.  A plan whose phases are being timed
+// launches them one by one.
+constexpr int kRunIters = 128;
+
+void iterate_run(ot_dyn_plan* p, const StepArgs& s, int iters) {
+    const bool whole = p->d.refine == OT_REFINE_CARRY && p->p1d && !p->prof_mask &&
+                       iterations_1d_ok(s, p->tab[0], p->tab[3]);
+    while (iters > 0) {
+        if (!whole) {
+            iterate(p, s, false);
+            iters -= 1;
+            continue;
+        }
+        const int n = std::min(iters, kRunIters);
+        launch_iterations_1d(s, p->tab[0], p->tab[1], p->tab[2], p->tab[3], p->tc64, p->tt64, n,
+                             std::max(0, std::min(n, p->d.carry_refine - p->it_next)), p->stream);
+        p->it_next += n;
+        iters -= n;
+    }
 }
 
 // Reduce the residual partials of the last check iteration and of the
@@ -807,6 +844,7 @@ int ot_dyn_create(const ot_dyn_desc* d, void* stream, void* workspace, size_t ws
             std::vector<double> h64((size_t)n * n + n);
             std::copy(M.begin(), M.end(), h64.begin());
             std::copy(lam.begin(), lam.end(), h64.begin() + (size_t)n * n);
+            if (a == 3 && d->Y == 1 && d->C == 1 && n <= 32) dc_table_1d(n, d->X, M, lam, h64);
             double* d64 = a == 2 ? p->tc64 : p->tt64;
             e = hipMemcpyAsync(d64, h64.data(), h64.size() * sizeof(double),
                                hipMemcpyHostToDevice, p->stream);
@@ -906,7 +944,7 @@ int ot_dyn_step(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc, int i
     if (!p || !F || !Mx || !My || !Mc || iters < 0) return OT_ERR_PARAM;
     if (!p->have_init) { p->err = "ot_dyn_init must succeed first"; return OT_ERR_STATE; }
     const StepArgs s = step_args(p, F, Mx, My, Mc);
-    for (int i = 0; i < iters; ++i) iterate(p, s, false);
+    iterate_run(p, s, iters);
     p->total_iters += iters;
     HIPCHK(p, hipGetLastError());
     return OT_OK;
@@ -951,7 +989,7 @@ int solve_loop(ot_dyn_plan* p, const StepArgs& s, int max_iters) {
     int done = 0, status = OT_NOT_CONVERGED;
     while (done < max_iters) {
         const int chunk = std::min(p->d.check_every, max_iters - done);
-        for (int i = 0; i + 1 < chunk; ++i) iterate(p, s, false);
+        iterate_run(p, s, chunk - 1);
         iterate(p, s, true);
         done += chunk;
         p->total_iters += chunk;
@@ -1091,9 +1129,10 @@ int ot_dyn_prox_eval(int kind, long long n, const float* am, const float* af, fl
 // ---- internal hooks for the batched solver (batch.cpp) ---------------------
 namespace otd {
 
-void plan_iterate(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc, bool check) {
+void plan_iterate(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc, int iters, bool check) {
     const StepArgs s = step_args(p, F, Mx, My, Mc);
-    iterate(p, s, check);
+    iterate_run(p, s, check ? iters - 1 : iters);
+    if (check) iterate(p, s, true);
 }
 
 int plan_collect(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc) {

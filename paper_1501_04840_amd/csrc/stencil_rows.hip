@@ -491,47 +491,6 @@ __global__ void __launch_bounds__(256) k_div_vec(StepArgs s) {
 // b), b and b_bar updates, for all colours of a node; residual partials when
 // CHECK.  NPHI 3 and 4 (carried potential) also add the potentials into Phi
 // at the own node.
-// FP64 residual sums of a check iteration (the RedSlot quantities).
-struct ResidSums {
-    double db2 = 0, z2 = 0, dx2 = 0, x2 = 0, jj = 0;
-};
-
-// Steps 2 and 3 of Algorithm 1 at one node, given the new x on the node's
-// lower and upper faces (mx0/mx1, my0/my1, mc0/mc1, f0/f1) and the dual bo:
-// z = prox of J at K x + c + bo, the new dual bn = K x + c + bo - z and its
-// extrapolation bbn = bn + theta (bn - bo).  With CHECK the residual sums take
-// the node's terms, o holding the old x on the lower faces (f at k = 0, the
-// boundary slice, counts as 0).
-template <bool CHECK>
-__device__ __forceinline__ void node_dual(float mx0, float mx1, float my0, float my1, float mc0,
-                                          float mc1, float f0, float f1, bool k0,
-                                          const float (&bo)[4], const float (&o)[4], float sigma,
-                                          float th, int prox, float (&bn)[4], float (&bbn)[4],
-                                          ResidSums& rs) {
-    // K x + c at the node, plus b
-    const float bx = bo[0], by = bo[1], bc = bo[2], bf = bo[3];
-    const float amx = 0.5f * (mx0 + mx1) + bx, amy = 0.5f * (my0 + my1) + by;
-    const float amc = 0.5f * (mc0 + mc1) + bc, amf = 0.5f * (f0 + f1) + bf;
-    float ux, uy, uc, vv;
-    prox_J(amx, amy, amc, amf, sigma, ux, uy, uc, vv, prox);
-    bn[0] = amx - ux; bn[1] = amy - uy; bn[2] = amc - uc; bn[3] = amf - vv;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) bbn[q] = bn[q] + th * (bn[q] - bo[q]);
-    if constexpr (CHECK) {
-        const float nf = k0 ? 0.f : f0;
-        const double ddx = (double)mx0 - o[0], ddy = (double)my0 - o[1];
-        const double ddc = (double)mc0 - o[2], ddf = (double)nf - o[3];
-        rs.dx2 += ddx * ddx + ddy * ddy + ddc * ddc + ddf * ddf;
-        rs.x2 += (double)mx0 * mx0 + (double)my0 * my0 + (double)mc0 * mc0 + (double)nf * nf;
-        const double ex = (double)bn[0] - bx, ey = (double)bn[1] - by;
-        const double ec = (double)bn[2] - bc, ef = (double)bn[3] - bf;
-        rs.db2 += ex * ex + ey * ey + ec * ec + ef * ef;
-        const double u2 = (double)ux * ux + (double)uy * uy + (double)uc * uc;
-        rs.z2 += u2 + (double)vv * vv;
-        rs.jj += vv > 0.f ? u2 / (2.0 * vv) : 0.0;
-    }
-}
-
 template <int CHECK, int NPHI_, int C, bool NT>
 __global__ void __launch_bounds__(256) k_update_rows(StepArgs s, int nxb) {
     constexpr int NPHI = NPHI_ == 4 ? 2 : (NPHI_ == 3 ? 1 : NPHI_);

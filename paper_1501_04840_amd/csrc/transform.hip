@@ -17,6 +17,7 @@
 #include "otd_common.h"
 #include "fft_common.h"
 #include "fft_lines.h"
+#include "stencil_common.h"
 
 #pragma clang fp contract(on)   // as in fft_common.h
 
@@ -639,6 +640,7 @@ static bool tc_reg_dispatch(const TcArgs& a, hipStream_t st) {
 // and adds it to the jx = 0 column, where after the inverse y transform it is
 // the same value at every y.
 
+constexpr int cmin(int a, int b) { return a < b ? a : b; }
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
 
 // LDS layout of the lines of length 256 in the fused passes: a row pitch of
@@ -983,53 +985,65 @@ __global__ void __launch_bounds__(NT) k_yt(TcArgs a) {
 // column along t in registers with the division by the eigenvalues, and the
 // rows back along x.  One launch instead of three for each iteration of the
 // batched 1D (hue) problems.
-template <int M1, int M2, int P, int NT, int KF, int KI>
-__global__ void __launch_bounds__(NT) k_p1d(TcArgs a) {
-    constexpr int L = 2 * M1 * M2, T = M2, PITCH = L + 1, NLINES = cmax(P, NT / T);
-    constexpr int NS = L * P / NT, S = NT / P;
-    static_assert(NS * NT == L * P, "tile must split into floats per thread");
-    static_assert(S * P == NT && S >= 2, "row-sum slots");
-    __shared__ __align__(16) float lds[NLINES * PITCH];
-    __shared__ double dsum[NT + 2 * P];
-    __shared__ float dcl[P];
-    const Geom& g = a.g;
-    const int b = blockIdx.x;
-    if (a.frz && a.frz[b] != 0.f) return;   // frozen problem (block-uniform)
-    float* base = a.R + (long long)b * g.nc;
-    // single floats, consecutive over the threads (conflict-free LDS writes)
-    float buf[NS];
+//
+// MIX: an axis whose length 2 M1 M2 has the factors 2,
+// 3 and 5 (the hue axes of 180 and 360 bins), with the mixed-radix transforms of
+// fft_lines.h instead (Hartley for periodic x, KF = KI = 2; DCT-II / DCT-III for
+// Neumann x).  NT is at least P M2, a multiple of 64.
+template <int M1, int M2, int P>
+struct Tile1d {
+    static constexpr int L = 2 * M1 * M2, PITCH = L + 1;
+    static_assert(L % 4 == 0, "rows of whole float4");
+    float lds[P * PITCH];
+    double sums[P];
+    float dcl[P];
+};
+
+// The solve of r in the tile, in place, by the block's threads tid, at least P M2.
+// Starts and ends with a barrier.
+//
+// The spatial-DC line is one FP64 product of the row sums with D (dc_table_1d):
+// G lanes per row, then per output, summed by shuffles (the same lanes whatever the
+// block's size, so the same rounding).
+template <int M1, int M2, int P, int NT, int KF, int KI, bool MIX>
+__device__ __forceinline__ void solve_1d(const TcArgs& a, Tile1d<M1, M2, P>& sm, int tid) {
+    using Tile = Tile1d<M1, M2, P>;
+    constexpr int L = Tile::L, PITCH = Tile::PITCH;
+    constexpr int G = (P * M2 + 63) / 64 * 64 / P >= 8 ? 8 : 4;
+    static_assert(NT % 64 == 0 && NT >= P * M2 && NT >= G * P, "block shape");
+    float* const lds = sm.lds;
+    const int o = tid / G, l = tid % G;
+    double d[P / G];
 #pragma unroll
-    for (int j = 0; j < NS; ++j) buf[j] = base[threadIdx.x + NT * j];
-    for (int e = P * PITCH + threadIdx.x; e < NLINES * PITCH; e += NT) lds[e] = 0.f;
+    for (int i = 0; i < P / G; ++i) d[i] = a.tt64[P * P + P + min(o, P - 1) * P + l + G * i];
+    __syncthreads();
+    if (o < P) {
+        double s = 0.0;
+#pragma unroll 8
+        for (int x = l; x < L; x += G) s += (double)lds[o * PITCH + x];
 #pragma unroll
-    for (int j = 0; j < NS; ++j) {
-        const int e = (int)threadIdx.x + NT * j;
-        lds[(e / L) * PITCH + (e % L)] = buf[j];
+        for (int m = G / 2; m > 0; m >>= 1) s += __shfl_xor(s, m, G);
+        if (l == 0) sm.sums[o] = s;
     }
     __syncthreads();
-    {   // FP64 sums of the time rows: S slots per row, then one thread per row
-        const int t = threadIdx.x / S, q = threadIdx.x - t * S;
-        double acc = 0.0;
-        for (int x = q; x < L; x += S) acc += (double)lds[t * PITCH + x];
-        dsum[threadIdx.x] = acc;
+    if (o < P) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < P / G; ++i) s += d[i] * sm.sums[l + G * i];
+#pragma unroll
+        for (int m = G / 2; m > 0; m >>= 1) s += __shfl_xor(s, m, G);
+        if (l == 0) sm.dcl[o] = (float)s;      // (the transform's barrier publishes it)
     }
-    __syncthreads();
-    double* d1 = dsum + NT;
-    if (threadIdx.x < P) {
-        double acc = 0.0;
-        for (int q = 0; q < S; ++q) acc += dsum[threadIdx.x * S + q];
-        d1[threadIdx.x] = acc;
-    }
-    __syncthreads();
-    dc_solve_fp64<P>(a, b, d1, dcl);
-    __syncthreads();
-    const int line = threadIdx.x / T, tt = threadIdx.x - line * T;
-    line_xform<M1, M2, KF>(lds + line * PITCH, tt, a.tx.tw);
-    for (int jx = threadIdx.x; jx < L; jx += NT) {
+    const int line = tid / M2, tt = tid - line * M2;
+    const bool act = line < P;
+    float* const sl = lds + (act ? line : 0) * PITCH;
+    if constexpr (MIX) line_xform_mix<M1, M2, KF>(sl, tt, a.tx.twm, act);
+    else line_xform<M1, M2, KF>(sl, tt, a.tx.tw, act);
+    for (int jx = tid; jx < L; jx += NT) {
         float u[P];
         if (jx == 0) {
 #pragma unroll
-            for (int t = 0; t < P; ++t) u[t] = dcl[t];
+            for (int t = 0; t < P; ++t) u[t] = sm.dcl[t];
         } else {
 #pragma unroll
             for (int t = 0; t < P; ++t) u[t] = lds[t * PITCH + jx];
@@ -1044,27 +1058,16 @@ __global__ void __launch_bounds__(NT) k_p1d(TcArgs a) {
         for (int t = 0; t < P; ++t) lds[t * PITCH + jx] = u[t];
     }
     __syncthreads();
-    line_xform<M1, M2, KI>(lds + line * PITCH, tt, a.tx.tw);
-#pragma unroll
-    for (int j = 0; j < NS; ++j) {
-        const int e = (int)threadIdx.x + NT * j;
-        base[e] = lds[(e / L) * PITCH + (e % L)];
-    }
+    if constexpr (MIX) line_xform_mix<M1, M2, KI>(sl, tt, a.tx.twm, act);
+    else line_xform<M1, M2, KI>(sl, tt, a.tx.tw, act);
 }
 
-// The one-block solve for an axis whose length 2 M1 M2 is not a power of
-// two but has only the factors 2, 3 and 5 (the hue axes of 180 and 360
-// bins): as k_p1d, with the mixed-radix transforms of fft_lines.h along x
-// (Hartley for periodic x, KF = KI = 2; DCT-II / DCT-III for Neumann x)
-// instead of the dense contraction on the matrix cores.  NT threads, a multiple of P and of 64, at least
-// P M2; the rows are staged as in k_p1d.
-template <int M1, int M2, int P, int NT, int KF, int KI>
-__global__ void __launch_bounds__(NT) k_p1d_mix(TcArgs a) {
-    constexpr int L = 2 * M1 * M2, T = M2, PITCH = L + 1, S = NT / P;
-    static_assert(L % 4 == 0 && S * P == NT && S >= 2 && P * T <= NT, "block shape");
-    __shared__ __align__(16) float lds[P * PITCH];
-    __shared__ double dsum[NT + 2 * P];
-    __shared__ float dcl[P];
+template <int M1, int M2, int P, int NT, int KF, int KI, bool MIX>
+__global__ void __launch_bounds__(NT) k_p1d(TcArgs a) {
+    using Tile = Tile1d<M1, M2, P>;
+    constexpr int L = Tile::L, PITCH = Tile::PITCH;
+    __shared__ Tile sm;
+    float* const lds = sm.lds;
     const Geom& g = a.g;
     const int b = blockIdx.x;
     if (a.frz && a.frz[b] != 0.f) return;   // frozen problem (block-uniform)
@@ -1076,58 +1079,242 @@ __global__ void __launch_bounds__(NT) k_p1d_mix(TcArgs a) {
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
         const int e = (int)threadIdx.x + NT * j;
-        buf[j] = e < L * P ? base[e] : 0.f;
+        buf[j] = base[e < L * P ? e : 0];
     }
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
         const int e = (int)threadIdx.x + NT * j;
         if (e < L * P) lds[(e / L) * PITCH + (e % L)] = buf[j];
     }
-    __syncthreads();
-    {   // FP64 sums of the time rows: S slots per row, then one thread per row
-        const int t = threadIdx.x / S, q = threadIdx.x - t * S;
-        double acc = 0.0;
-        for (int x = q; x < L; x += S) acc += (double)lds[t * PITCH + x];
-        dsum[threadIdx.x] = acc;
-    }
-    __syncthreads();
-    double* d1 = dsum + NT;
-    if (threadIdx.x < P) {
-        double acc = 0.0;
-        for (int q = 0; q < S; ++q) acc += dsum[threadIdx.x * S + q];
-        d1[threadIdx.x] = acc;
-    }
-    __syncthreads();
-    dc_solve_fp64<P>(a, b, d1, dcl);
-    __syncthreads();
-    const int line = threadIdx.x / T, tt = threadIdx.x - line * T;
-    const bool act = line < P;
-    float* const sl = lds + (act ? line : 0) * PITCH;
-    line_xform_mix<M1, M2, KF>(sl, tt, a.tx.twm, act);
-    for (int jx = threadIdx.x; jx < L; jx += NT) {
-        float u[P];
-        if (jx == 0) {
-#pragma unroll
-            for (int t = 0; t < P; ++t) u[t] = dcl[t];
-        } else {
-#pragma unroll
-            for (int t = 0; t < P; ++t) u[t] = lds[t * PITCH + jx];
-            dct2_reg<P>(u, a.twt);
-            const float lx = a.tx.lam[jx];
-#pragma unroll
-            for (int jt = 0; jt < P; ++jt)
-                u[jt] = u[jt] * __builtin_amdgcn_rcpf(lx + a.tt.lam[jt]);   // lx > 0 off the DC
-            dct3_reg<P>(u, a.twt);
-        }
-#pragma unroll
-        for (int t = 0; t < P; ++t) lds[t * PITCH + jx] = u[t];
-    }
-    __syncthreads();
-    line_xform_mix<M1, M2, KI>(sl, tt, a.tx.twm, act);
+    solve_1d<M1, M2, P, NT, KF, KI, MIX>(a, sm, threadIdx.x);
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
         const int e = (int)threadIdx.x + NT * j;
         if (e < L * P) base[e] = lds[(e / L) * PITCH + (e % L)];
+    }
+}
+
+// Whole iterations of a problem with one spatial axis (Y = C = 1, Neumann y; the
+// carried potential, no residual check), `iters` of them in one launch: a block
+// owns a problem, and every quantity an iteration's steps exchange stays inside
+// it, so the steps are separated by barriers instead of launches and r and the
+// potential stay in LDS.  The first `refined` iterations take the refinement
+// solve.  The same expressions per node as k_div_rows, k_update_rows and
+// k_p1d, four nodes along x per thread and step.
+//
+// The faces along y and colour are walls or absent: My and Mc are zero, and the
+// duals b_y, b_c and their extrapolations stay zero once they are, so after an
+// iteration that left them zero (in the whole block) they are neither read nor
+// written.  An iteration then moves 19 words per node instead of 39.
+//
+// A hue batch of 1024 problems (64..360 bins, 16 or 32 steps; ten shapes):
+// 300 iterations of them 63 -> 36 ms, of 64 problems 45 -> 27, of 8 38 -> 15.  What
+// bounds a block: the latency of its loads and of the transforms between barriers
+// (360 x 32, 100 problems: 36 us an iteration, half of it in the solve); what
+// bounds many: memory (400 of those problems: 75 us, 4.7 TB/s).  Fewer registers by
+// launch bounds (spills), requesting the next nodes' loads ahead (spills), one
+// launch for several shapes (spills, equal time) and a product on the matrix cores
+// along t (equal time) did not pay.
+template <int M1, int M2, int P, int NT, int KF, int KI, bool MIX>
+__global__ void __launch_bounds__(NT) k_iter_1d(TcArgs a, StepArgs s, int iters, int refined) {
+    using Tile = Tile1d<M1, M2, P>;
+    constexpr int L = Tile::L, PITCH = Tile::PITCH, VL = L / 4, NV = VL * P;
+    __shared__ __align__(16) Tile sm;
+    float* const phi = sm.lds;                 // r, then the potential
+    const Geom& g = s.g;
+    const int b = blockIdx.x;
+    if (s.frz_run && s.frz_run[b] != 0.f) return;   // frozen problem (block-uniform)
+    const long long c0 = (long long)b * g.nc, f0 = (long long)b * g.nf;
+    float* const F = s.F + f0;
+    float* const Mx = s.Mx + c0;
+    float* const A0 = s.A[0] + c0;
+    float* const A3 = s.A[3] + c0;
+    float* const R = s.R + c0;
+    float* const Phi = s.Phi + c0;
+    auto ld4 = [](const float* p) { return *reinterpret_cast<const float4*>(p); };
+    auto st4 = [](float* p, const float (&v)[4]) {
+        *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+    };
+    const float ts = 0.5f * s.tau_sigma, th = s.theta, sigma = s.sig[b];
+    bool idle = false;                         // b_y, b_c and their extrapolations are zero
+    for (int it = 0; it < iters; ++it) {
+        // (what the steps derive from the thread's number is formed anew in each:
+        // held over the iterations it takes the registers of a whole wave)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        // a = x - tau sigma K^T b_bar + grad Phi, r = A a - f_b^-
+#pragma unroll 1
+        for (int v = tid; v < NV; v += NT) {
+            const int k = v / VL, x = 4 * (v - k * VL), i = k * L + x;
+            const bool k0 = k == 0, k1 = k + 1 == P;
+            const int im = k * L + (x == 0 ? L - 1 : x - 1), ip = k * L + (x + 4 == L ? 0 : x + 4);
+            const int tm = k0 ? i : i - L, tp = k1 ? i : i + L;    // clamped time steps
+            const float4 X = ld4(Mx + i), T0 = ld4(F + i), T1 = ld4(F + i + L);
+            const float4 B = ld4(s.bb[0] + c0 + i);
+            const float4 Bm = ld4(s.bb[3] + c0 + tm), Bc = ld4(s.bb[3] + c0 + i), Bp = ld4(s.bb[3] + c0 + tp);
+            const float4 Q = ld4(Phi + i), Qm = ld4(Phi + tm), Qp = ld4(Phi + tp);
+            const float xv[5] = {X.x, X.y, X.z, X.w, Mx[ip]};
+            const float bv[6] = {s.bb[0][c0 + im], B.x, B.y, B.z, B.w, s.bb[0][c0 + ip]};
+            const float qv[6] = {Phi[im], Q.x, Q.y, Q.z, Q.w, Phi[ip]};
+            const float t0[4] = {T0.x, T0.y, T0.z, T0.w}, t1[4] = {T1.x, T1.y, T1.z, T1.w};
+            const float bm[4] = {Bm.x, Bm.y, Bm.z, Bm.w}, bc[4] = {Bc.x, Bc.y, Bc.z, Bc.w};
+            const float bp[4] = {Bp.x, Bp.y, Bp.z, Bp.w}, qm[4] = {Qm.x, Qm.y, Qm.z, Qm.w};
+            const float qp[4] = {Qp.x, Qp.y, Qp.z, Qp.w};
+            float o0[4], o3[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float qc = qv[e + 1];
+                float ax0 = xv[e] - ts * (bv[e] + bv[e + 1]);
+                float ax1 = xv[e + 1] - ts * (bv[e + 1] + bv[e + 2]);
+                float af0 = t0[e] - ts * (bm[e] + bc[e]);
+                float af1 = t1[e] - ts * (bc[e] + bp[e]);
+                ax0 += g.sx * (qc - qv[e]);
+                ax1 += g.sx * (qv[e + 2] - qc);
+                af0 += g.st * (qc - qm[e]);
+                af1 += g.st * (qp[e] - qc);
+                ax0 = !g.perx && x + e == 0 ? 0.f : ax0;
+                ax1 = !g.perx && x + e + 1 == L ? 0.f : ax1;
+                af0 = k0 ? t0[e] : af0;        // boundary slices are data
+                af1 = k1 ? t1[e] : af1;
+                phi[k * PITCH + x + e] = fmaf(g.st, af1 - af0, g.sx * (ax1 - ax0));
+                o0[e] = ax0;
+                o3[e] = k0 ? 0.f : af0;
+            }
+            st4(A0 + i, o0);
+            st4(A3 + i, o3);
+        }
+        solve_1d<M1, M2, P, NT, KF, KI, MIX>(a, sm, tid);
+        const bool two = it < refined;         // uniform
+        if (two) {
+            // r'' = A (a + grad phi_1) - f_b^-, phi_2 from it; phi_1 in R
+    #pragma unroll 1
+        for (int v = tid; v < NV; v += NT) {
+                const int k = v / VL, x = 4 * (v - k * VL);
+                const float* const q = phi + k * PITCH + x;
+                const float o[4] = {q[0], q[1], q[2], q[3]};
+                st4(R + k * L + x, o);
+            }
+            __syncthreads();
+    #pragma unroll 1
+        for (int v = tid; v < NV; v += NT) {
+                const int k = v / VL, x = 4 * (v - k * VL), i = k * L + x;
+                const bool k0 = k == 0, k1 = k + 1 == P;
+                const int im = k * L + (x == 0 ? L - 1 : x - 1), ip = k * L + (x + 4 == L ? 0 : x + 4);
+                const int tm = k0 ? i : i - L, tp = k1 ? i : i + L;
+                const float4 X = ld4(A0 + i);
+                const float4 T0 = k0 ? ld4(F + i) : ld4(A3 + i), T1 = k1 ? ld4(F + i + L) : ld4(A3 + i + L);
+                const float4 Q = ld4(R + i), Qm = ld4(R + tm), Qp = ld4(R + tp);
+                const float xv[5] = {X.x, X.y, X.z, X.w, A0[ip]};
+                const float qv[6] = {R[im], Q.x, Q.y, Q.z, Q.w, R[ip]};
+                const float t0[4] = {T0.x, T0.y, T0.z, T0.w}, t1[4] = {T1.x, T1.y, T1.z, T1.w};
+                const float qm[4] = {Qm.x, Qm.y, Qm.z, Qm.w}, qp[4] = {Qp.x, Qp.y, Qp.z, Qp.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float pc = qv[e + 1];
+                    const float ax0 = !g.perx && x + e == 0 ? 0.f : xv[e] + g.sx * (pc - qv[e]);
+                    const float ax1 = !g.perx && x + e + 1 == L ? 0.f : xv[e + 1] + g.sx * (qv[e + 2] - pc);
+                    const float af0 = k0 ? t0[e] : t0[e] + g.st * (pc - qm[e]);
+                    const float af1 = k1 ? t1[e] : t1[e] + g.st * (qp[e] - pc);
+                    phi[k * PITCH + x + e] = fmaf(g.st, af1 - af0, g.sx * (ax1 - ax0));
+                }
+            }
+            solve_1d<M1, M2, P, NT, KF, KI, MIX>(a, sm, tid);
+        }
+        // x = a + grad phi_1 (+ grad phi_2), prox, duals
+        bool any = false;
+#pragma unroll 1
+        for (int v = tid; v < NV; v += NT) {
+            const int k = v / VL, x = 4 * (v - k * VL), i = k * L + x;
+            const bool k0 = k == 0, k1 = k + 1 == P;
+            const int xm = x == 0 ? L - 1 : x - 1, xp = x + 4 == L ? 0 : x + 4;
+            const int tm = k0 ? k : k - 1, tp = k1 ? k : k + 1;
+            const float4 X = ld4(A0 + i);
+            const float4 T0 = k0 ? ld4(F + i) : ld4(A3 + i), T1 = k1 ? ld4(F + i + L) : ld4(A3 + i + L);
+            const float4 B0 = ld4(s.b[0] + c0 + i), B3 = ld4(s.b[3] + c0 + i), Q = ld4(Phi + i);
+            float4 B1 = make_float4(0.f, 0.f, 0.f, 0.f), B2 = B1;
+            if (!idle) {
+                B1 = ld4(s.b[1] + c0 + i);
+                B2 = ld4(s.b[2] + c0 + i);
+            }
+            const float xv[5] = {X.x, X.y, X.z, X.w, A0[k * L + xp]};
+            const float t0[4] = {T0.x, T0.y, T0.z, T0.w}, t1[4] = {T1.x, T1.y, T1.z, T1.w};
+            const float b0[4] = {B0.x, B0.y, B0.z, B0.w}, b1[4] = {B1.x, B1.y, B1.z, B1.w};
+            const float b2[4] = {B2.x, B2.y, B2.z, B2.w}, b3[4] = {B3.x, B3.y, B3.z, B3.w};
+            const float qo[4] = {Q.x, Q.y, Q.z, Q.w};
+            // differences of the potentials along x and t: of the latest in LDS, and
+            // with the refinement those of phi_1 first
+            const float* const q = phi + k * PITCH;
+            float pv[6] = {q[xm], q[x], q[x + 1], q[x + 2], q[x + 3], q[xp]}, pm[4], pp[4];
+            float dx[5], d0[4], d1[4], add[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                pm[e] = phi[tm * PITCH + x + e];
+                pp[e] = phi[tp * PITCH + x + e];
+            }
+            if (two) {
+                const int im = k * L + xm, ip = k * L + xp;
+                const float4 C = ld4(R + i), Cm = ld4(R + tm * L + x), Cp = ld4(R + tp * L + x);
+                const float cv[6] = {R[im], C.x, C.y, C.z, C.w, R[ip]};
+                const float cm[4] = {Cm.x, Cm.y, Cm.z, Cm.w}, cp[4] = {Cp.x, Cp.y, Cp.z, Cp.w};
+#pragma unroll
+                for (int e = 0; e < 5; ++e) dx[e] = (cv[e + 1] - cv[e]) + (pv[e + 1] - pv[e]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    d0[e] = (cv[e + 1] - cm[e]) + (pv[e + 1] - pm[e]);
+                    d1[e] = (cp[e] - cv[e + 1]) + (pp[e] - pv[e + 1]);
+                    add[e] = cv[e + 1] + pv[e + 1];
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 5; ++e) dx[e] = pv[e + 1] - pv[e];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    d0[e] = pv[e + 1] - pm[e];
+                    d1[e] = pp[e] - pv[e + 1];
+                    add[e] = pv[e + 1];
+                }
+            }
+            float n[4][4], nb[4][4], vx[4], vf[4], vq[4];
+            bool kept = true;
+            ResidSums rs;                      // unused: no residual check here
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float mx0 = !g.perx && x + e == 0 ? 0.f : xv[e] + g.sx * dx[e];
+                const float mx1 = !g.perx && x + e + 1 == L ? 0.f : xv[e + 1] + g.sx * dx[e + 1];
+                const float fa = k0 ? t0[e] : t0[e] + g.st * d0[e];
+                const float fb = k1 ? t1[e] : t1[e] + g.st * d1[e];
+                const float bo[4] = {b0[e], b1[e], b2[e], b3[e]}, o[4] = {0.f, 0.f, 0.f, 0.f};
+                float bn[4], bbn[4];
+                node_dual<false>(mx0, mx1, 0.f, 0.f, 0.f, 0.f, fa, fb, k0, bo, o, sigma, th, s.prox, bn,
+                                 bbn, rs);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) { n[c][e] = bn[c]; nb[c][e] = bbn[c]; }
+                kept = kept && bn[1] == 0.f && bn[2] == 0.f && bbn[1] == 0.f && bbn[2] == 0.f;
+                vx[e] = mx0; vf[e] = fa; vq[e] = qo[e] + add[e];
+            }
+            any = any || !kept;
+            st4(s.b[0] + c0 + i, n[0]);
+            st4(s.b[3] + c0 + i, n[3]);
+            st4(s.bb[0] + c0 + i, nb[0]);
+            st4(s.bb[3] + c0 + i, nb[3]);
+            if (!idle || !kept) {
+                st4(s.b[1] + c0 + i, n[1]);
+                st4(s.b[2] + c0 + i, n[2]);
+                st4(s.bb[1] + c0 + i, nb[1]);
+                st4(s.bb[2] + c0 + i, nb[2]);
+            }
+            if (it == 0) {
+                const float z[4] = {0.f, 0.f, 0.f, 0.f};
+                st4(s.My + c0 + i, z);
+                st4(s.Mc + c0 + i, z);
+            }
+            st4(Mx + i, vx);
+            if (!k0) st4(F + i, vf);
+            st4(Phi + i, vq);
+        }
+        // (the barrier also ends the block's reads of the tile and its writes of
+        // the state)
+        idle = !__syncthreads_or(any ? 1 : 0);
     }
 }
 
@@ -1245,41 +1432,49 @@ __global__ void __launch_bounds__(kP1dDenseThreads) k_p1d_dense(TcArgs a, int Lp
     }
 }
 
-template <int M1, int M2, int P>
-static void p1d_launch(const TcArgs& a, hipStream_t st) {
-    constexpr int NT = cmax(64, P * M2);
+// iters > 0: that many iterations of k_iter_1d, the first `refined` refined; else the
+// solve of r.
+struct Run1d {
+    const StepArgs* s;
+    int iters, refined;
+};
+
+template <int M1, int M2, int P, int KF, int KI, bool MIX>
+static void p1d_start(const TcArgs& a, const Run1d& run, hipStream_t st) {
+    constexpr int NT = (P * M2 + 63) / 64 * 64;
+    // the steps besides the transforms take about two steps of four nodes per thread
+    constexpr int NI = cmax(NT, cmin(512, (M1 * M2 * P / 4 + 63) / 64 * 64));
     const dim3 grid((unsigned)a.g.B);
-    if (a.g.perx)
-        hipLaunchKernelGGL((k_p1d<M1, M2, P, NT, 2, 2>), grid, dim3(NT), 0, st, a);
+    if (run.iters > 0)
+        hipLaunchKernelGGL((k_iter_1d<M1, M2, P, NI, KF, KI, MIX>), grid, dim3(NI), 0, st, a, *run.s,
+                           run.iters, run.refined);
     else
-        hipLaunchKernelGGL((k_p1d<M1, M2, P, NT, 0, 1>), grid, dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((k_p1d<M1, M2, P, NT, KF, KI, MIX>), grid, dim3(NT), 0, st, a);
 }
 
+template <int M1, int M2, int P, bool MIX>
+static void p1d_launch(const TcArgs& a, const Run1d& run, hipStream_t st) {
+    if (a.g.perx) p1d_start<M1, M2, P, 2, 2, MIX>(a, run, st);
+    else p1d_start<M1, M2, P, 0, 1, MIX>(a, run, st);
+}
+
+// The lengths of the fast and mixed-radix one-block transforms.
 template <int P>
-static bool p1d_dispatch(const TcArgs& a, hipStream_t st) {
+static void p1d_dispatch(const TcArgs& a, const Run1d& run, hipStream_t st) {
     switch (a.g.X) {
-        case 64: p1d_launch<8, 4, P>(a, st); return true;
-        case 128: p1d_launch<8, 8, P>(a, st); return true;
-        case 256: p1d_launch<16, 8, P>(a, st); return true;
-        default: return false;
+        case 64: p1d_launch<8, 4, P, false>(a, run, st); break;
+        case 128: p1d_launch<8, 8, P, false>(a, run, st); break;
+        case 256: p1d_launch<16, 8, P, false>(a, run, st); break;
+        case 100: p1d_launch<5, 10, P, true>(a, run, st); break;
+        case 180: p1d_launch<6, 15, P, true>(a, run, st); break;
+        default: p1d_launch<12, 15, P, true>(a, run, st); break;     // 360
     }
 }
 
-template <int M1, int M2, int P>
-static void p1d_mix_launch(const TcArgs& a, hipStream_t st) {
-    constexpr int NT0 = P * M2, NT = (NT0 + 63) / 64 * 64;
-    static_assert(NT % P == 0, "row-sum slots");
-    if (a.g.perx)
-        hipLaunchKernelGGL((k_p1d_mix<M1, M2, P, NT, 2, 2>), dim3((unsigned)a.g.B), dim3(NT), 0, st, a);
-    else
-        hipLaunchKernelGGL((k_p1d_mix<M1, M2, P, NT, 0, 1>), dim3((unsigned)a.g.B), dim3(NT), 0, st, a);
-}
-
-template <int P>
-static void p1d_mix_dispatch(const TcArgs& a, hipStream_t st) {
-    if (a.g.X == 100) p1d_mix_launch<5, 10, P>(a, st);
-    else if (a.g.X == 180) p1d_mix_launch<6, 15, P>(a, st);
-    else p1d_mix_launch<12, 15, P>(a, st);
+static void p1d_run(const TcArgs& a, const Run1d& run, hipStream_t st) {
+    if (a.g.P == 8) p1d_dispatch<8>(a, run, st);
+    else if (a.g.P == 16) p1d_dispatch<16>(a, run, st);
+    else p1d_dispatch<32>(a, run, st);
 }
 
 bool poisson_1d_ok(const Geom& g, const AxisTab& tx, const AxisTab& tt) {
@@ -1305,21 +1500,32 @@ void launch_poisson_1d(const Geom& g, float* R, const AxisTab& tx, const AxisTab
     a.tt64 = tt64;
     a.frz = frz;
     a.twt = tt.tw;
-    if (!tx.tw && tx.twm) {
-        if (g.P == 8) p1d_mix_dispatch<8>(a, st);
-        else if (g.P == 16) p1d_mix_dispatch<16>(a, st);
-        else p1d_mix_dispatch<32>(a, st);
+    if (tx.tw || tx.twm) {
+        p1d_run(a, Run1d{nullptr, 0, 0}, st);
         return;
     }
-    if (!tx.tw) {
-        if (g.P == 8) p1d_dense_launch<8>(a, st);
-        else if (g.P == 16) p1d_dense_launch<16>(a, st);
-        else p1d_dense_launch<32>(a, st);
-        return;
-    }
-    if (g.P == 8) p1d_dispatch<8>(a, st);
-    else if (g.P == 16) p1d_dispatch<16>(a, st);
-    else p1d_dispatch<32>(a, st);
+    if (g.P == 8) p1d_dense_launch<8>(a, st);
+    else if (g.P == 16) p1d_dense_launch<16>(a, st);
+    else p1d_dense_launch<32>(a, st);
+}
+
+bool iterations_1d_ok(const StepArgs& s, const AxisTab& tx, const AxisTab& tt) {
+    if (!poisson_1d_ok(s.g, tx, tt) || !(tx.tw || tx.twm) || s.g.pery || !s.Phi) return false;
+    uintptr_t any = (uintptr_t)s.F | (uintptr_t)s.Mx | (uintptr_t)s.My | (uintptr_t)s.Mc | (uintptr_t)s.R |
+                    (uintptr_t)s.Phi;
+    for (int q = 0; q < 4; ++q) any |= (uintptr_t)s.b[q] | (uintptr_t)s.bb[q] | (uintptr_t)s.A[q];
+    return any % 16 == 0;          // 16-byte accesses
+}
+
+void launch_iterations_1d(const StepArgs& s, const AxisTab& tx, const AxisTab& ty, const AxisTab& tc,
+                          const AxisTab& tt, const double* tc64, const double* tt64, int iters,
+                          int refined, hipStream_t st) {
+    TcArgs a{};
+    a.g = s.g; a.R = s.R; a.tx = tx; a.ty = ty; a.tc = tc; a.tt = tt;
+    a.tc64 = tc64;
+    a.tt64 = tt64;
+    a.twt = tt.tw;
+    p1d_run(a, Run1d{&s, iters, refined}, st);
 }
 
 // Time slices per block of the x passes: all of them (blocks of half the
