@@ -40,7 +40,9 @@ struct Group {
     std::vector<int> members;      // problem ids in group order
     hipStream_t side = nullptr;
     ot_dyn_plan* plan = nullptr;
-    size_t off_state = 0, off_plan = 0, plan_bytes = 0;
+    size_t off_state = 0, off_plan = 0, plan_bytes = 0, off_table = 0;
+    const long long *at_h = nullptr, *at_F = nullptr, *at_M = nullptr;   // packed offsets of the
+                                                                         // members (device)
     float *F = nullptr, *Mx = nullptr, *My = nullptr, *Mc = nullptr;
     float *f0 = nullptr, *f1 = nullptr;
     bool active = true;
@@ -109,6 +111,8 @@ int make_plan(const ot_dyn_desc* base, int count, const int* dims, Plan* out) {
         g.off_plan = o;
         g.plan_bytes = pb;
         o = align_up(o + pb);
+        g.off_table = o;
+        o = align_up(o + 3 * (size_t)B * sizeof(long long));
     }
     P.total = o;
     P.off_h.assign(count + 1, 0);
@@ -166,6 +170,13 @@ void drop_graph(ot_dyn_batch* bt) {
     bt->graph = nullptr;
     bt->graph_groups.clear();
     bt->graph_chunk = 0;
+}
+
+// A group's states to (1) or from (0) the packed arrays, on its stream.
+void copy_state(const Group& g, float* F, float* M, int to_packed) {
+    const int n = (int)g.members.size();
+    launch_copy_members({g.at_F, F, {g.F}, g.nf(), to_packed}, n, 1, g.side);
+    launch_copy_members({g.at_M, M, {g.Mx, g.My, g.Mc}, g.nc(), to_packed}, n, 3, g.side);
 }
 
 // Capture `chunk` iterations (the last one with residual partials) of every
@@ -279,6 +290,20 @@ int ot_dyn_batch_create(const ot_dyn_desc* base, int count, const int* dims, voi
         st = ot_dyn_create(&g.d, g.side, bt->ws + g.off_plan, g.plan_bytes, &g.plan);
         if (st != OT_OK) return fail(st);
         plan_enable_freeze(g.plan);
+        const size_t n = g.members.size();
+        std::vector<long long> at(3 * n);
+        for (size_t j = 0; j < n; ++j) {
+            at[j] = bt->P.off_h[g.members[j]];
+            at[n + j] = bt->P.off_F[g.members[j]];
+            at[2 * n + j] = bt->P.off_M[g.members[j]];
+        }
+        long long* table = (long long*)(bt->ws + g.off_table);
+        if (hipMemcpyAsync(table, at.data(), at.size() * sizeof(long long), hipMemcpyHostToDevice,
+                           g.side) != hipSuccess || hipStreamSynchronize(g.side) != hipSuccess)
+            return fail(OT_ERR_HIP);
+        g.at_h = table;
+        g.at_F = table + n;
+        g.at_M = table + 2 * n;
         g.conv_iter.assign(g.members.size(), -1);
         g.fell_back.assign(g.members.size(), 0);
         g.rep.assign(g.members.size(), ot_dyn_report{});
@@ -303,14 +328,10 @@ int ot_dyn_batch_set_boundary(ot_dyn_batch* bt, const float* f0, const float* f1
     bt->have_boundary = false;
     BCHK(bt, hipStreamSynchronize(bt->user));      // inputs were produced on the caller's stream
     for (auto& g : bt->P.groups) {
-        const size_t bytes = g.slice() * sizeof(float);
-        for (size_t j = 0; j < g.members.size(); ++j) {
-            const int i = g.members[j];
-            BCHK(bt, hipMemcpyAsync(g.f0 + j * g.slice(), f0 + bt->P.off_h[i], bytes,
-                                    hipMemcpyDeviceToDevice, g.side));
-            BCHK(bt, hipMemcpyAsync(g.f1 + j * g.slice(), f1 + bt->P.off_h[i], bytes,
-                                    hipMemcpyDeviceToDevice, g.side));
-        }
+        const int n = (int)g.members.size();
+        launch_copy_members({g.at_h, const_cast<float*>(f0), {g.f0}, g.slice(), 0}, n, 1, g.side);
+        launch_copy_members({g.at_h, const_cast<float*>(f1), {g.f1}, g.slice(), 0}, n, 1, g.side);
+        BCHK(bt, hipGetLastError());
         const int st = ot_dyn_set_boundary(g.plan, g.f0, g.f1);
         if (st != OT_OK) {
             bt->err = ot_dyn_last_error(g.plan);
@@ -535,19 +556,9 @@ int ot_dyn_batch_problem(const ot_dyn_batch* bt, int i, ot_dyn_report* rep) {
 
 int ot_dyn_batch_get_state(ot_dyn_batch* bt, float* F, float* M) {
     if (!bt || !F || !M) return OT_ERR_PARAM;
-    for (auto& g : bt->P.groups) {
-        for (size_t j = 0; j < g.members.size(); ++j) {
-            const int i = g.members[j];
-            BCHK(bt, hipMemcpyAsync(F + bt->P.off_F[i], g.F + j * g.nf(), g.nf() * sizeof(float),
-                                    hipMemcpyDeviceToDevice, g.side));
-            float* m = M + bt->P.off_M[i];
-            const float* src[3] = {g.Mx, g.My, g.Mc};
-            for (int q = 0; q < 3; ++q)
-                BCHK(bt, hipMemcpyAsync(m + q * g.nc(), src[q] + j * g.nc(), g.nc() * sizeof(float),
-                                        hipMemcpyDeviceToDevice, g.side));
-        }
-        BCHK(bt, hipStreamSynchronize(g.side));
-    }
+    for (auto& g : bt->P.groups) copy_state(g, F, M, 1);
+    BCHK(bt, hipGetLastError());
+    for (auto& g : bt->P.groups) BCHK(bt, hipStreamSynchronize(g.side));
     return OT_OK;
 }
 
@@ -564,16 +575,8 @@ int ot_dyn_batch_set_state(ot_dyn_batch* bt, const float* F, const float* M, int
     bt->warm = false;
     BCHK(bt, hipStreamSynchronize(bt->user));      // the state was produced on the caller's stream
     for (auto& g : bt->P.groups) {
-        for (size_t j = 0; j < g.members.size(); ++j) {
-            const int i = g.members[j];
-            BCHK(bt, hipMemcpyAsync(g.F + j * g.nf(), F + bt->P.off_F[i], g.nf() * sizeof(float),
-                                    hipMemcpyDeviceToDevice, g.side));
-            const float* m = M + bt->P.off_M[i];
-            float* dst[3] = {g.Mx, g.My, g.Mc};
-            for (int q = 0; q < 3; ++q)
-                BCHK(bt, hipMemcpyAsync(dst[q] + j * g.nc(), m + q * g.nc(), g.nc() * sizeof(float),
-                                        hipMemcpyDeviceToDevice, g.side));
-        }
+        copy_state(g, const_cast<float*>(F), const_cast<float*>(M), 0);
+        BCHK(bt, hipGetLastError());
         const int st = ot_dyn_init(g.plan, mode, g.F, g.Mx, g.My, g.Mc);
         if (st != OT_OK) {
             bt->err = ot_dyn_last_error(g.plan);

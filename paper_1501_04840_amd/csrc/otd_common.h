@@ -304,6 +304,18 @@ int plan_restart_cold(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc,
 // packed [4][P][C][Y][X] array; asynchronous on the plan's stream.
 int plan_copy_dual(ot_dyn_plan* p, int b, float* packed, int to_packed);
 
+// ---- batches (stencil.hip) ------------------------------------------------
+// Pieces of len floats between a packed array (member j: off[j], device; its
+// parts behind one another) and up to three group arrays (member j: j len).
+struct MemberCopy {
+    const long long* off;
+    float* packed;
+    float* part[3];
+    long long len;
+    int to_packed;
+};
+void launch_copy_members(const MemberCopy& m, int members, int parts, hipStream_t st);
+
 // ---- reductions (stencil.hip) ------------------------------------------
 // out[q] = sum_j part[q * n + j] in FP64, for q < nq.
 void launch_reduce(const double* part, long long n, int nq, double* out, hipStream_t st);
