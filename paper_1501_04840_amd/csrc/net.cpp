@@ -418,6 +418,25 @@ int warm_check(const ot_dyn_desc* d, int batch) {
 
 }  // namespace
 
+namespace {
+
+// Every layer between the flat exchange layout and the padded one.
+void map_params(ot_net* n, float* padded, float* flat, int to_padded) {
+    ParamMaps q{};
+    for (size_t i = 0; i < n->layers.size(); ++i) {
+        const auto& l = n->layers[i];
+        float* const p = padded + l.off_p;
+        float* const o = flat + l.off_o;
+        q.l[q.n++] = {to_padded ? o : p, to_padded ? p : o, l.taps, l.cin_o, l.cout_o, l.cin_p, l.cout_p};
+        if (q.n == kParamMaps || i + 1 == n->layers.size()) {
+            launch_param_maps(q, to_padded, n->st);
+            q.n = 0;
+        }
+    }
+}
+
+}  // namespace
+
 extern "C" {
 
 int ot_net_default_desc(int H, int W, int in_ch, int out_ch, int max_batch, ot_net_desc* d) {
@@ -483,9 +502,7 @@ int ot_net_create(const ot_net_desc* d, void* stream, void* workspace, size_t ws
 
 int ot_net_set_params(ot_net* n, const float* params) {
     if (!n || !params) return OT_ERR_PARAM;
-    for (auto& l : n->layers)
-        launch_param_map(params + l.off_o, n->master + l.off_p, l.taps, l.cin_o, l.cout_o, l.cin_p,
-                         l.cout_p, 1, n->st);
+    map_params(n, n->master, const_cast<float*>(params), 1);
     hipError_t e = hipMemsetAsync(n->mom1, 0, n->np_p * 4, n->st);
     if (e == hipSuccess) e = hipMemsetAsync(n->mom2, 0, n->np_p * 4, n->st);
     if (e != hipSuccess) return hipfail(n, e, "reset moments");
@@ -497,9 +514,7 @@ int ot_net_set_params(ot_net* n, const float* params) {
 
 int ot_net_get_params(ot_net* n, float* params) {
     if (!n || !params) return OT_ERR_PARAM;
-    for (auto& l : n->layers)
-        launch_param_map(n->master + l.off_p, params + l.off_o, l.taps, l.cin_o, l.cout_o, l.cin_p,
-                         l.cout_p, 0, n->st);
+    map_params(n, n->master, params, 0);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? OT_OK : hipfail(n, e, "get_params");
 }
@@ -518,9 +533,7 @@ int ot_net_grad(ot_net* n, int batch, const float* x, const float* t, const floa
     const int st = loss_and_grad(n, batch, x, t, cw, loss);
     if (st != OT_OK) return st;
     if (grad) {
-        for (auto& l : n->layers)
-            launch_param_map(n->grad + l.off_p, grad + l.off_o, l.taps, l.cin_o, l.cout_o, l.cin_p,
-                             l.cout_p, 0, n->st);
+        map_params(n, n->grad, grad, 0);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hipfail(n, e, "grad export");
     }

@@ -74,8 +74,17 @@ void launch_adam(float* p, float* m, float* v, const float* g, long long n, floa
                  float b2, float eps, float c1, float c2, hipStream_t st);
 void launch_export(const float* w, int taps, int cin, int cout, bf16_t* wf, bf16_t* wb,
                    hipStream_t st);
-void launch_param_map(const float* src, float* dst, int taps, int cin_o, int cout_o, int cin_p,
-                      int cout_p, int to_padded, hipStream_t st);
+struct ParamMap {
+    const float* src;
+    float* dst;
+    int taps, cin_o, cout_o, cin_p, cout_p;
+};
+constexpr int kParamMaps = 32;       // layers per launch
+struct ParamMaps {
+    int n;
+    ParamMap l[kParamMaps];
+};
+void launch_param_maps(const ParamMaps& q, int to_padded, hipStream_t st);
 
 // solver glue
 struct WarmGeom {

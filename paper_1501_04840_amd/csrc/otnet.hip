@@ -846,26 +846,44 @@ __device__ inline double block_sum_d(double v) {
 
 constexpr int kLossPer = 16;    // elements per thread of the loss kernel
 
-// dy = d loss / d y (BF16, padded channels 0) and the loss per block (FP64).
+// dy = d loss / d y (BF16, padded channels 0) and the loss per block (FP64).  A
+// thread's loads are clamped, not skipped, so that eight elements' are in flight;
+// waited for one element at a time, with 64-bit divisions, 32 targets of 64 x 64 x
+// 189 took 60 us, now 40.
+template <typename I>
 __global__ void __launch_bounds__(kThreads) k_loss(const float* y, const float* t, const float* cw,
                                                   int out_ch, int out_p, long long npix,
                                                   bf16_t* dy, double* part) {
-    const long long n = npix * out_p;
-    const long long base = (long long)blockIdx.x * kThreads * kLossPer;
+    constexpr int U = 8;
+    const I n = (I)(npix * out_p), base = (I)blockIdx.x * kThreads * kLossPer + threadIdx.x;
     const double inv = 1.0 / (double)npix;
     double s = 0.0;
-    for (int e = 0; e < kLossPer; ++e) {
-        const long long i = base + (long long)e * kThreads + threadIdx.x;
-        if (i >= n) break;
-        const long long p = i / out_p;
-        const int c = (int)(i - p * out_p);
-        float g = 0.f;
-        if (c < out_ch) {
-            const float d = y[p * out_ch + c] - t[p * out_ch + c];
-            s += (double)cw[c] * (double)d * (double)d * inv;
-            g = (float)(2.0 * cw[c] * inv) * d;
+    for (int h = 0; h < kLossPer / U; ++h) {
+        float yv[U], tv[U], w[U];
+        bool in[U];                            // a channel of the target, not padding
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const I i = base + (I)(h * U + u) * kThreads;
+            const I p = i / (I)out_p;
+            const int c = (int)(i - p * (I)out_p);
+            in[u] = i < n && c < out_ch;
+            const long long o = in[u] ? (long long)p * out_ch + c : 0;
+            yv[u] = y[o];
+            tv[u] = t[o];
+            w[u] = cw[in[u] ? c : 0];
         }
-        dy[i] = f2bf(g);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const I i = base + (I)(h * U + u) * kThreads;
+            if (i >= n) break;
+            float g = 0.f;
+            if (in[u]) {
+                const float d = yv[u] - tv[u];
+                s += (double)w[u] * (double)d * (double)d * inv;
+                g = (float)(2.0 * w[u] * inv) * d;
+            }
+            dy[i] = f2bf(g);
+        }
     }
     s = block_sum_d(s);
     if (threadIdx.x == 0) part[blockIdx.x] = s;
@@ -917,29 +935,32 @@ __global__ void __launch_bounds__(kThreads) k_export(const float* w, int taps, i
     (back ? wb : wf)[i] = h;
 }
 
-// One layer between the flat exchange layout (cin_o, cout_o) and the padded
-// device layout (cin_p, cout_p); padded entries read as 0.
-__global__ void __launch_bounds__(kThreads) k_param_map(const float* src, float* dst, int taps,
-                                                       int cin_o, int cout_o, int cin_p,
-                                                       int cout_p, int to_padded) {
-    const long long np = (long long)taps * cin_p * cout_p + cout_p;
-    const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= np) return;
-    const long long nw = (long long)taps * cin_p * cout_p;
-    long long o = -1;
-    if (i < nw) {
-        const int co = (int)(i % cout_p);
-        const int ci = (int)((i / cout_p) % cin_p);
-        const int tap = (int)(i / ((long long)cout_p * cin_p));
-        if (co < cout_o && ci < cin_o) o = ((long long)tap * cin_o + ci) * cout_o + co;
-    } else {
-        const int co = (int)(i - nw);
-        if (co < cout_o) o = (long long)taps * cin_o * cout_o + co;
+// Layers between the flat exchange layout (cin_o, cout_o) and the padded device
+// layout (cin_p, cout_p), blockIdx.y the layer; padded entries read as 0.  (A
+// launch per layer: 20 of 3 us for the network of the 64 x 64 problems.)
+__global__ void __launch_bounds__(kThreads) k_param_map(ParamMaps q, int to_padded) {
+    const ParamMap& l = q.l[blockIdx.y];
+    const unsigned cin_p = l.cin_p, cout_p = l.cout_p;
+    const long long nw = (long long)l.taps * cin_p * cout_p, np = nw + cout_p;
+    for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < np;
+         i += (long long)gridDim.x * kThreads) {
+        long long o = -1;
+        if (i < nw) {
+            const bool small = nw < (1LL << 32);          // 32-bit divisions
+            const long long row = small ? (long long)((unsigned)i / cout_p) : i / cout_p;
+            const int co = (int)(i - row * cout_p);
+            const int tap = (int)(small ? (unsigned)row / cin_p : row / cin_p);
+            const int ci = (int)(row - (long long)tap * cin_p);
+            if (co < l.cout_o && ci < l.cin_o) o = ((long long)tap * l.cin_o + ci) * l.cout_o + co;
+        } else {
+            const int co = (int)(i - nw);
+            if (co < l.cout_o) o = (long long)l.taps * l.cin_o * l.cout_o + co;
+        }
+        if (to_padded)
+            l.dst[i] = o >= 0 ? l.src[o] : 0.f;
+        else if (o >= 0)
+            l.dst[o] = l.src[i];
     }
-    if (to_padded)
-        dst[i] = o >= 0 ? src[o] : 0.f;
-    else if (o >= 0)
-        dst[o] = src[i];
 }
 
 // ---- solver glue ----------------------------------------------------------
@@ -1351,8 +1372,13 @@ int loss_blocks(long long n) { return (int)((n + kThreads * kLossPer - 1) / (kTh
 
 void launch_loss(const float* y, const float* t, const float* cw, int out_ch, int out_p,
                  long long npix, bf16_t* dy, double* part, hipStream_t st) {
-    hipLaunchKernelGGL(k_loss, dim3(loss_blocks(npix * out_p)), dim3(kThreads), 0, st, y, t, cw,
-                       out_ch, out_p, npix, dy, part);
+    const long long n = npix * out_p;
+    if (n < (1LL << 31) - kThreads * kLossPer)
+        hipLaunchKernelGGL(k_loss<unsigned>, dim3(loss_blocks(n)), dim3(kThreads), 0, st, y, t, cw, out_ch,
+                           out_p, npix, dy, part);
+    else
+        hipLaunchKernelGGL(k_loss<long long>, dim3(loss_blocks(n)), dim3(kThreads), 0, st, y, t, cw,
+                           out_ch, out_p, npix, dy, part);
 }
 
 void launch_sum(const double* part, int n, double* out, hipStream_t st) {
@@ -1371,11 +1397,8 @@ void launch_export(const float* w, int taps, int cin, int cout, bf16_t* wf, bf16
     hipLaunchKernelGGL(k_export, dim3(blocks(n)), dim3(kThreads), 0, st, w, taps, cin, cout, wf, wb);
 }
 
-void launch_param_map(const float* src, float* dst, int taps, int cin_o, int cout_o, int cin_p,
-                      int cout_p, int to_padded, hipStream_t st) {
-    const long long n = (long long)taps * cin_p * cout_p + cout_p;
-    hipLaunchKernelGGL(k_param_map, dim3(blocks(n)), dim3(kThreads), 0, st, src, dst, taps, cin_o,
-                       cout_o, cin_p, cout_p, to_padded);
+void launch_param_maps(const ParamMaps& q, int to_padded, hipStream_t st) {
+    hipLaunchKernelGGL(k_param_map, dim3(256, q.n), dim3(kThreads), 0, st, q, to_padded);
 }
 
 void launch_warm_inputs(const WarmGeom& g, int nb, const float* f0, const float* f1,
