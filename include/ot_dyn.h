@@ -337,15 +337,17 @@ const char* ot_dyn_batch_last_error(const ot_dyn_batch* bt);
  * harnesses that forbid hipMalloc): Algorithm 1 from its cold start to the
  * certificate, as ot_dyn_create + ot_dyn_set_boundary + ot_dyn_init
  * (OT_INIT_COLD) + ot_dyn_solve + ot_dyn_destroy, with the plan's workspace
- * in a device array of OT_DYN_STATIC_BYTES owned by the library (one per
+ * in a device array owned by the library (one per
  * GPU, held until the process ends) instead of the caller's.  The caller
  * passes inputs and outputs only: f0, f1 [batch][C][Y][X] and F, Mx, My, Mc
  * (layouts above), device pointers on the current device; `stream` as in
  * ot_dyn_create.  Results are those of the calls it stands for.  Calls no
  * hipMalloc, hipFree or other allocating routine.  Synchronous.
- * Returns OT_ERR_SHAPE when ot_dyn_workspace_size(d) exceeds
- * OT_DYN_STATIC_BYTES (e.g. 64 x 64 x 3 x 16 needs 12.2 MiB, 128 x 128 x 3
- * x 16 49 MiB: use ot_dyn_create with a workspace), OT_ERR_PARAM for null
+ * Returns OT_ERR_SHAPE when ot_dyn_workspace_size(d), less the matrices of
+ * the dense transforms (up to 4 MiB for sides without a fast one, for which the
+ * array has room of its own), exceeds OT_DYN_STATIC_BYTES (e.g. 64 x 64 x 3 x 16
+ * needs 12.2 MiB, 128 x 128 x 3 x 16 49 MiB: use ot_dyn_create with a
+ * workspace), OT_ERR_PARAM for null
  * pointers or max_iters < 1, else the status of ot_dyn_solve.  Every call
  * on one GPU uses the same array: calls that overlap on one GPU (several
  * host threads or streams) race and must be serialised by the caller. */

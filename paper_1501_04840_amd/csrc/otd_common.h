@@ -277,7 +277,11 @@ void launch_cols_fast(float* R, long long outer, long long inner, int L, const f
 }  // namespace otd
 struct ot_dyn_plan;
 struct ot_dyn_report;
+struct ot_dyn_desc;
 namespace otd {
+// Workspace of a plan without the transform matrices that only speed it up: what
+// ot_dyn_solve_static's limit is compared with.
+size_t plan_least_bytes(const ot_dyn_desc& d);
 // `iters` iterations, the last with residual partials when `check`.
 void plan_iterate(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc, int iters, bool check);
 int plan_collect(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc);

@@ -188,7 +188,9 @@ bool dense3_pays(const Geom& g) {
     return !(fx && fy) && !(fx && g.X > 180) && !(fy && g.Y > 180);
 }
 
-Layout layout_of(const ot_dyn_desc& d) {
+// tables false: without the matrices of the dense three-pass solve and the
+// one-axis DC table (plan_least_bytes).
+Layout layout_of(const ot_dyn_desc& d, bool tables = true) {
     const Geom g = make_geom(d);
     Layout L;
     const long long ncT = (long long)g.B * g.nc;
@@ -208,11 +210,11 @@ Layout layout_of(const ot_dyn_desc& d) {
         L.off_tab[a] = take((2 * (size_t)ns[a] * ns[a] + ns[a]) * sizeof(float));
         L.off_tw[a] = take((4 * (size_t)ns[a] + ns[a] / 2) * 2 * sizeof(float));
     }
-    const bool dense = dense3_pays(g);
+    const bool dense = tables && dense3_pays(g);
     L.off_dense[0] = take(dense ? dense_axis_floats(d.X, g.perx) * sizeof(float) : 0);
     L.off_dense[1] = take(dense ? dense_axis_floats(d.Y, g.pery) * sizeof(float) : 0);
     L.off_tc64 = take(((size_t)d.C * d.C + d.C) * sizeof(double));
-    const size_t dc = d.Y == 1 && d.C == 1 && d.P <= 32 ? (size_t)d.P * d.P : 0;    // dc_table_1d
+    const size_t dc = tables && d.Y == 1 && d.C == 1 && d.P <= 32 ? (size_t)d.P * d.P : 0;   // dc_table_1d
     L.off_tt64 = take(((size_t)d.P * d.P + d.P + dc) * sizeof(double));
     // FP64 partials: per-node kernels write one per 256 nodes of a plane; the
     // row kernels one per row segment and colour (plane stride Y * nxb)
@@ -1144,6 +1146,8 @@ int plan_collect(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc) {
     p->last_res = worst;
     return st;
 }
+
+size_t plan_least_bytes(const ot_dyn_desc& d) { return layout_of(d, false).total; }
 
 void plan_apply_tuning(ot_dyn_plan* p, int row_bx, int dense_xy) { apply_tuning(p, row_bx, dense_xy); }
 
