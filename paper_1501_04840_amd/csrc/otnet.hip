@@ -137,24 +137,38 @@ __global__ void __launch_bounds__(64 * WP * WN) k_conv(ConvArgs a, ConvGeom g) {
                 if (e0 + j * NT < g.entries) tile[at[j]] = in[j] ? v[j] : make_uint4(0, 0, 0, 0);
         }
     }
-    // Where each step's K entries lie, relative to a pixel's first unit: the
-    // byte offset in the tile (or the unit and tap of an unstaged source) of
-    // unit k8 = 2 s + half at steps[half][s], for nsteps rounded up to whole
-    // groups and one group more (those read the pixel's own first unit).  The
-    // K loop reads a group's offsets with a few 16-byte LDS loads instead of
-    // walking taps and channels.
+    // Where each step's K entries lie in the staged tile, relative to a pixel's
+    // first unit: the byte offset of unit k8 = 2 s + half at steps[half][s], for
+    // nsteps rounded up to whole groups and one group more (those read the
+    // pixel's own first unit).  The K loop reads a group's offsets with a few
+    // 16-byte LDS loads instead of walking taps and channels.
     const int nk8 = a.K >> 3, nsteps = (nk8 + 1) >> 1, tab = conv_table(nsteps, AHEAD);
     int* const steps = reinterpret_cast<int*>(tile + (STAGED ? ti * g.iu : 0));
-    for (int e = threadIdx.x; e < 2 * tab; e += NT) {
-        const int h = e >= tab ? 1 : 0, k8 = 2 * (e - h * tab) + h;
-        int o = 0;
-        if (k8 < nk8) {
-            const int tap = g.nc8 == 1 ? k8 : (int)__umulhi(k8, g.mc), cu = k8 - tap * g.nc8;
-            const int dy = tap / 3, dx = tap - 3 * dy;
-            o = STAGED ? 16 * (dy * g.ru + dx * g.pu + cu) : (cu << 4) | tap;
+    if (STAGED)
+        for (int e = threadIdx.x; e < 2 * tab; e += NT) {
+            const int h = e >= tab ? 1 : 0, k8 = 2 * (e - h * tab) + h;
+            int o = 0;
+            if (k8 < nk8) {
+                const int tap = g.nc8 == 1 ? k8 : (int)__umulhi(k8, g.mc), cu = k8 - tap * g.nc8;
+                const int dy = tap / 3, dx = tap - 3 * dy;
+                o = 16 * (dy * g.ru + dx * g.pu + cu);
+            }
+            steps[e] = o;
         }
-        steps[e] = o;
-    }
+    // An unstaged source has no table (its length would grow with the channels):
+    // the loads come in the order of the steps and walk the unit and the tap of
+    // this half's next step (past K: a unit of the image that no product uses).
+    int wc = half, wt = 0;
+    auto walk = [&](int n) {
+        wc += n;
+#pragma unroll
+        for (int q = 0; q < 2; ++q)                      // (one channel unit: two taps a step)
+            if (wc >= g.nc8) {
+                wc -= g.nc8;
+                ++wt;
+            }
+    };
+    walk(0);
     // this lane's pixel of each fragment
     int base[PF], row0[PF], col0[PF];
     long long pix[PF];                                   // pixel index, -1 outside
@@ -184,7 +198,7 @@ __global__ void __launch_bounds__(64 * WP * WN) k_conv(ConvArgs a, ConvGeom g) {
             for (int f = 0; f < PF; ++f)
                 fa[f] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const char*>(tile) + base[f] + o);
         } else {
-            const int cu = o >> 4, tap = o & 15, dy = tap / 3 - 1, dx = tap - 3 * (tap / 3) - 1;
+            const int dy = wt / 3 - 1, dx = wt - 3 * (wt / 3) - 1;
 #pragma unroll
             for (int f = 0; f < PF; ++f) {
                 uint4 v = make_uint4(0, 0, 0, 0);
@@ -192,9 +206,10 @@ __global__ void __launch_bounds__(64 * WP * WN) k_conv(ConvArgs a, ConvGeom g) {
                 const bool in = pix[f] >= 0 &&
                                 (one || ((unsigned)y < (unsigned)a.H && (unsigned)x < (unsigned)a.W));
                 const long long q = one ? pix[f] : pix[f] + (long long)dy * a.W + dx;
-                if (in) v = *reinterpret_cast<const uint4*>(a.src + q * a.src_ld + 8 * cu);
+                if (in) v = *reinterpret_cast<const uint4*>(a.src + q * a.src_ld + 8 * wc);
                 fa[f] = *reinterpret_cast<const bf16x8*>(&v);
             }
+            walk(2);
         }
     };
     const int nf = blockIdx.y * WN + wn, n0 = nf * 32;
@@ -223,11 +238,15 @@ __global__ void __launch_bounds__(64 * WP * WN) k_conv(ConvArgs a, ConvGeom g) {
     // products (the scheduling barriers keep them there).
     const int4* so = reinterpret_cast<const int4*>(steps + half * tab);
     constexpr int G4 = AHEAD / 4;
-    int4 on[G4];
+    int4 on[G4] = {};
     int oc[AHEAD];
     bf16x8 fa[2][PF];
+    auto request = [&] {                                 // a group's offsets
+        if (STAGED)
 #pragma unroll
-    for (int q = 0; q < G4; ++q) on[q] = so[q];
+            for (int q = 0; q < G4; ++q) on[q] = so[q];
+    };
+    request();
     load_a(fa[0], on[0].x);
     int s = 0;
     auto take = [&] {                                    // this group's offsets; the next one's loads
@@ -239,8 +258,7 @@ __global__ void __launch_bounds__(64 * WP * WN) k_conv(ConvArgs a, ConvGeom g) {
             oc[4 * q + 3] = on[q].w;
         }
         so += G4;
-#pragma unroll
-        for (int q = 0; q < G4; ++q) on[q] = so[q];
+        request();
     };
     const int whole = nk8 >> 1;                          // steps wholly inside K
     for (; s + AHEAD <= whole; s += AHEAD) {
@@ -355,7 +373,7 @@ void conv_launch_a(const ConvArgs& a, const ConvGeom& g, hipStream_t st) {
     if (lds <= kConvLds && g.entries < 65536)
         hipLaunchKernelGGL((k_conv<PF, WP, WN, AHEAD, true, EPI>), grid, block, lds, st, a, g);
     else
-        hipLaunchKernelGGL((k_conv<PF, WP, WN, AHEAD, false, EPI>), grid, block, tab, st, a, g);
+        hipLaunchKernelGGL((k_conv<PF, WP, WN, AHEAD, false, EPI>), grid, block, 0, st, a, g);
 }
 
 template <int PF, int WP, int WN, int EPI>
