@@ -288,15 +288,15 @@ int conv_wgrad(ot_net* n, int li, int nb, int lev, View src, const bf16_t* dz) {
     a.M = l.taps * l.cin_p + 1;
     a.N = l.cout_p;
     a.K = nb * a.H * a.W;
-    const int splits = wgrad_splits(a.taps, a.cin, a.N, nb, a.H, a.W);
-    if ((long long)splits * a.M * a.N > n->part_cap) {
+    const int most = wgrad_splits(a.taps, a.cin, a.N, nb, a.H, a.W);
+    if ((long long)most * a.M * a.N > n->part_cap) {
         n->err = "internal: weight-gradient partials exceed the workspace";
         return OT_ERR_SHAPE;
     }
     a.dst = n->part;
     a.dst_ld = a.N;
     a.dst_n = a.N;
-    launch_wgrad(a, splits, n->st);
+    const int splits = launch_wgrad(a, n->st);
     launch_wgrad_reduce(n->part, splits, a.M, a.N, n->grad + l.off_p, n->st);
     return OT_OK;
 }

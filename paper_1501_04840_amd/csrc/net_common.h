@@ -53,10 +53,11 @@ struct View {
 };
 
 void launch_conv(const ConvArgs& a, int epi, hipStream_t st);
-// Splits of a weight gradient over the pixels (partials of taps cin + 1 rows
+// Most splits of a weight gradient over the pixels (partials of taps cin + 1 rows
 // of cout each); never more for a smaller nb.
 int wgrad_splits(int taps, int cin, int cout, int nb, int H, int W);
-void launch_wgrad(const ConvArgs& a, int splits, hipStream_t st);
+// Returns the splits launched (partials to sum).
+int launch_wgrad(const ConvArgs& a, hipStream_t st);
 void launch_wgrad_reduce(const float* part, int splits, int M, int N, float* out, hipStream_t st);
 void launch_pack_input(const float* x, int in_ch, long long npix, bf16_t* out, int ld,
                        hipStream_t st);
