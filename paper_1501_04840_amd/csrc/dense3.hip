@@ -23,7 +23,7 @@
 // They replace five passes (rows, columns, colour and time, columns, rows) whose
 // kernels waited for their staging loads one by one, read the matrices with no
 // load ahead and did the products along t one scalar load per term: at 173 x 131
-// x 3 x 12 an iteration took 128 us, 102 of them in the solve; now 80.  What bounds
+// x 3 x 12 an iteration took 128 us, 102 of them in the solve; now 77.  What bounds
 // a pass at such sizes: launch and the latency of one block's loads, then the
 // products (unfolded they were 85 us).  A few problems of 16 x 16 x 3 x 8: 45 us
 // per iteration, now 28.
@@ -59,7 +59,7 @@ struct DenseArgs {
     double* part;              // FP64 plane partials of r, plane stride nbx
     int nbx;
     const float* frz;          // per problem: nonzero = frozen, skipped (or null)
-    int nsb;                   // plane-sum blocks of the forward x pass
+    int nsb;                   // plane-sum blocks of the forward x pass (a multiple of 8)
     int nrg, tb;               // x passes: time groups of a row y, times in each
     int lpb;                   // y and time pass: lines (jx, colour mode) per block
 };
@@ -180,8 +180,12 @@ __device__ __forceinline__ void product(float* tile, int pitch, const DenseAxis&
 }
 
 // One x pass of a row index y and a group of times (rows n = c tb + t - t0, 16 RT
-// of them).  The rows y go to the XCDs in contiguous eighths, so that the pieces
-// of the transposed scratch one L2 holds are longer runs.
+// of them).  Blocks go to the XCDs round-robin: each XCD takes a contiguous
+// eighth of the (row y, time group) items, times fastest, so that the pieces of
+// the transposed scratch one L2 holds are longer runs.  (The plane-sum blocks
+// ahead of them are a multiple of eight, the same shift for every XCD.)  With the
+// time groups of a row on XCDs of their own 173 x 131 x 3 x 12 took 79.6 us an
+// iteration, now 76.8; 128 x 128 x 3 x 12 55.3 and 53.0; from 400 x 400 on 1%.
 template <int RT, int MI, bool INV>
 __global__ void __launch_bounds__(kDThreads) k_dx(DenseArgs a) {
     extern __shared__ __attribute__((aligned(16))) float xs[];
@@ -194,9 +198,9 @@ __global__ void __launch_bounds__(kDThreads) k_dx(DenseArgs a) {
     const DenseAxis ax = a.ax;
     const int X = g.X, P = g.P, C = g.C, H = ax.H, width = ax.fold ? 2 * H : H, pitch = width + 4;
     const int h = ax.fold ? (X + 1) / 2 : X, nth = blockDim.x, W = nth >> 6;
-    const int blk = blockIdx.x - (INV ? 0 : a.nsb), hw = blk / a.nrg, tg = blk - hw * a.nrg;
-    const int nyb = g.Y * g.B, xcd = hw & 7, slot = hw >> 3, q8 = nyb >> 3, r8 = nyb & 7;
-    const int yb = xcd * q8 + min(xcd, r8) + slot, b = yb / g.Y, y = yb - b * g.Y;
+    const int blk = blockIdx.x - (INV ? 0 : a.nsb), items = g.Y * g.B * a.nrg;
+    const int xcd = blk & 7, item = xcd * (items >> 3) + min(xcd, items & 7) + (blk >> 3);
+    const int yb = item / a.nrg, tg = item - yb * a.nrg, b = yb / g.Y, y = yb - b * g.Y;
     if (a.frz && a.frz[b] != 0.f) return;      // block-uniform
     const int t0 = tg * a.tb, nt = min(a.tb, P - t0), nr = C * nt;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -639,7 +643,8 @@ void launch_dense3(const Geom& g, float* R, float* Rt, const AxisTab& tx, const 
     int rt;
     a.nrg = dx_groups(g, &rt);
     a.tb = (g.P + a.nrg - 1) / a.nrg;
-    a.nsb = pass == 0 ? (int)(((long long)g.B * g.P * g.C + kSumPlanesPerBlock - 1) / kSumPlanesPerBlock) : 0;
+    const long long planes = (long long)g.B * g.P * g.C, per8 = 8 * kSumPlanesPerBlock;
+    a.nsb = pass == 0 ? (int)((planes + per8 - 1) / per8 * 8) : 0;
     const unsigned blocks = (unsigned)(a.nsb + (long long)g.Y * g.B * a.nrg);
     const size_t lds = axis_lds(g.X, g.perx, rt);
     if (pass == 0) dx_dispatch<false>(a, rt, blocks, lds, st);
