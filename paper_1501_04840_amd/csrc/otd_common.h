@@ -213,6 +213,11 @@ void launch_fused_x(const Geom& g, float* R, float* Rt, const AxisTab& tx,
 void launch_fused_yt(const Geom& g, float* Rt, const AxisTab& tx, const AxisTab& ty,
                      const AxisTab& tc, const AxisTab& tt, hipStream_t st);
 
+// Longest axis of the matrix-core transforms of rows and columns (32 rows of Lp + 1
+// floats stay under 64 KB), and of the one-block solve's.
+constexpr int kMfmaRowsMaxL = 480;
+constexpr int kP1dDenseMaxL = 416;
+
 // Dense three-pass solve (dense3.hip) for x and y of any length up to 512 and P
 // <= 64.  An axis's matrices in fragment order: blocks of H positions (folded,
 // Neumann axes longer than 16: even and odd frequencies), H a multiple of 16.

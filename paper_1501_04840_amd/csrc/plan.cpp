@@ -164,28 +164,68 @@ int validate(const ot_dyn_desc* d, std::string* why) {
     return OT_OK;
 }
 
-// The dense three-pass solve is taken where the five passes would have a dense
-// one among them: a side without a fast or mixed-radix transform, or colours and
-// times without a register transform.  Us per iteration, five passes against
-// three: 173 x 131 x 3 x 12 128 and 80, 50 x 70 x 3 x 10 76 and 35,
-// 300 x 500 x 3 x 12 (periodic x) 2095 and 583, 173 x 64 x 3 x 16 71 and 50; fast
-// sides with P = 12 128 x 128 x 3 68 and 55, 180 x 100 x 3 x 20 122 and 98.  The
-// five passes stay for fast sides where the dense products grow with the sides
-// (P = 12: 256 x 256 x 3 143 and 156, 512 x 512 x 3 533 and 644; times and colours in
-// registers: 100 x 100 x 3 x 32 74 and 83, 360 x 100 x 3 x 32 periodic 191 and
-// 274); a fast side over 180 with times in registers (512 x 90 x 3 x 32 245 and
-// 309, 256 x 131 x 3 x 16 109 and 134); and many problems of a tile or two
-// (24 x 24 x 3 x 16, 64 of them, 113 and 121; 33 x 31 x 3 x 16, 32 of them, 118 and
-// 100; 16 x 16 x 3 x 12, 512 of them, 484 and 507).
+// The dense three-pass solve against the passes per axis (two of x, two of y, one of
+// colours and times): it saves launches and, along a side without a fast or
+// mixed-radix transform or with times and colours without a register transform, work;
+// it costs products over whole tiles, so a thin side, a long fast one, an unfolded
+// (periodic) axis or half-empty tiles lose it once there is enough to do.  The
+// microseconds an iteration gains are estimated as
+//   base + (per node terms below) nodes / 10^6
+// with a row of coefficients per kind of sides and times, least squares over 5500
+// measured shapes: sides 2 to 512, C 1 to 4, P 8 to 64, 10^3 to 2 10^7 nodes in 1 to
+// 1024 problems.  Us per iteration, passes per axis against three: 16 x 16 x 3 x 8
+// 47 and 28 (64 of them 62 and 62), 173 x 131 x 3 x 12 126 and 77, 173 x 64 x 3 x 16 71
+// and 48, 500 x 500 x 3 x 16 6030 and 838, 128 x 128 x 3 x 12 68 and 53; but 200 x 180 x 3
+// x 8, 8 of them, 440 and 478, 128 x 40 x 3 x 16, 4 of them, 84 and 98, 16 x 100 x 3 x 32, 16
+// of them, 143 and 176.  Of the shapes it picks 1% are more than 6% slower for it
+// (worst 23%), of those it leaves 1% would be more than 7% faster; with cuts by side and
+// rows alone 8% were more than 6% slower.
+// One axis (Y = 1 or X = 1), where the other axis of a tile is padding, by measured
+// cuts: 360 x 1 x 1 x 24, 100 of them, took 72 us per axis and 229 in three passes,
+// 1 x 180 x 3 x 16, 32 of them, 186 and 286; 150 x 1 x 1 x 24, 16 of them, 61 and 46.
+// Past the matrix-core passes per axis (500 x 1 x 1 x 12 589 and 50), and for a thin x
+// with a long y (2 x 300 x 3 x 16, 32 of them, 638 and 477), always three passes.
+// Fast sides over 180 with times in registers (512 x 90 x 3 x 32 245 and 309), two fast
+// sides of more than 320 together (512 x 512 x 3 x 12 533 and 644) keep the passes per axis.
+struct DenseGain {
+    float base, x32, y32;                   // x32, y32: added for a side of 32 at most
+    float node, x, y, inv_x, inv_y;         // per node: 1, X / 100, Y / 100, 10 / X, 10 / Y
+    float rows, unfolded, times;            // padded rows of a time group, unfolded sides / 100,
+};                                          // P / 10 (times in registers: C P < 16)
+constexpr DenseGain kDenseGain[2][2][2] = {     // [times in registers][x fast][y fast]
+    {{{36.6f, -5.4f, -6.1f, 34.4f, 2.3f, -0.5f, -20.5f, -7.4f, -20.3f, -2.8f, 2.3f},
+      {29.1f, -8.3f, 0.f, 30.7f, 2.6f, -2.1f, -28.2f, -13.1f, -29.3f, 0.f, 6.8f}},
+     {{19.6f, 0.f, -5.6f, 11.1f, -1.5f, 3.5f, 21.9f, -3.2f, -14.6f, -1.f, 5.7f},
+      {13.1f, 0.f, 0.f, 27.6f, -2.6f, -3.f, -17.5f, -29.9f, -16.4f, -0.9f, 4.f}}},
+    {{{21.6f, -5.7f, -4.5f, 9.4f, 4.1f, 3.1f, -21.7f, -8.2f, -9.1f, -3.5f, -8.1f},
+      {16.5f, -10.1f, 0.f, -8.3f, 3.8f, 4.2f, -24.3f, 57.7f, -8.2f, -2.f, -5.9f}},
+     {{6.4f, -0.1f, -6.5f, 5.1f, -3.8f, 5.5f, 4.9f, -0.8f, -9.8f, -3.8f, 0.f}, {}}}};
+
 bool dense3_pays(const Geom& g) {
     if (!dense3_ok(g)) return false;
     const auto fast = [](int n) { return fast_len(n) || mix_len(n); };
     const bool fx = fast(g.X), fy = fast(g.Y);
     const bool times = (g.P == 8 || g.P == 16 || g.P == 32) && (g.C == 1 || g.C == 3);
-    const int side = times ? 40 : 16, rows = times ? 1024 : 4096;
-    if (std::max(g.X, g.Y) <= side && (long long)g.Y * g.B >= rows) return false;
-    if (!times) return !fx || !fy || g.X + g.Y <= 320;
-    return !(fx && fy) && !(fx && g.X > 180) && !(fy && g.Y > 180);
+    const double nodes = 1e-6 * g.B * (double)g.nc;
+    if ((!fx && g.X > kMfmaRowsMaxL) || (!fy && g.Y > kMfmaRowsMaxL)) return true;
+    if (!fx && !fy && g.X <= 32 && g.Y >= 256) return true;
+    if (g.X == 1) return g.Y > 1 && !times && nodes <= 0.016;
+    if (g.Y == 1) {
+        if (times && g.C == 1 && g.X <= kP1dDenseMaxL) return false;    // the one-block solve
+        if (fx) return !times && g.C * g.P >= 32 && (g.P > 32 || g.X <= 256) && nodes <= 6e-4 * g.X;
+        return nodes <= (g.X > kP1dDenseMaxL ? 1.5e-3 : times ? 8e-4 : 1.1e-3) * g.X;
+    }
+    if (fx && fy && (times || g.X + g.Y > 320)) return false;
+    if (times && ((fx && g.X > 180) || (fy && g.Y > 180))) return false;
+    const DenseGain& a = kDenseGain[times][fx][fy];
+    const int cp = g.C * g.P;
+    const double rows = 16.0 * ((cp + 15) / 16) / cp, X = g.X, Y = g.Y;
+    const double unfolded = ((g.perx ? X : 0.0) + (g.pery ? Y : 0.0)) / 100;
+    const double base = a.base + (g.X <= 32 ? a.x32 : 0.f) + (g.Y <= 32 ? a.y32 : 0.f);
+    const double node = a.node + a.x * X / 100 + a.y * Y / 100 + a.inv_x * 10 / X + a.inv_y * 10 / Y +
+                        a.rows * rows + a.unfolded * unfolded +
+                        a.times * (times ? (cp < 16 ? 1.0 : 0.0) : g.P / 10.0);
+    return base + node * nodes > 0.0;
 }
 
 // tables false: without the matrices of the dense three-pass solve and the

@@ -60,7 +60,6 @@ __global__ void __launch_bounds__(kT) k_rows(float* R, long long rows, AxisTab t
 // + r % 4, column l % 32 of the tile).  The matrix operand comes from L2 in
 // chunks of 16 steps whose loads are all in flight before the chunk's MFMAs.
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-constexpr int kMfmaRowsMaxL = 480;     // 32 rows of Lp + 1 floats stay under 64 KB
 
 __device__ __forceinline__ int mfma_row(int r, int half) { return (r >> 2) * 8 + half * 4 + (r & 3); }
 
@@ -1319,7 +1318,7 @@ __global__ void __launch_bounds__(NT) k_iter_1d(TcArgs a, StepArgs s, int iters,
 }
 
 // The same one-block solve for one spatial axis without a fast transform
-// (e.g. 180 or 360 periodic bins), X <= kMfmaRowsMaxL: the P time rows,
+// (e.g. 90 or 150 periodic bins), X <= kP1dDenseMaxL: the P time rows,
 // padded with zero rows to 32, are the A operand of the dense x contraction
 // on the matrix cores (as in k_rows_mfma: 2 Lp threads, one wave per 32
 // output columns), forward and inverse, with the time pass and the FP64 DC
@@ -1329,7 +1328,6 @@ __global__ void __launch_bounds__(NT) k_iter_1d(TcArgs a, StepArgs s, int iters,
 // so Lp <= 512; X <= 416 keeps the dynamic LDS (32 padded rows of Lp + 1
 // floats plus the FP64 scratch) under 64 KB.
 constexpr int kP1dDenseThreads = 512;
-constexpr int kP1dDenseMaxL = 416;
 
 template <int P>
 __global__ void __launch_bounds__(kP1dDenseThreads) k_p1d_dense(TcArgs a, int Lp) {
