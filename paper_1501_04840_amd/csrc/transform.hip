@@ -1508,10 +1508,21 @@ void launch_poisson_1d(const Geom& g, float* R, const AxisTab& tx, const AxisTab
 }
 
 bool iterations_1d_ok(const StepArgs& s, const AxisTab& tx, const AxisTab& tt) {
-    if (!poisson_1d_ok(s.g, tx, tt) || !(tx.tw || tx.twm) || s.g.pery || !s.Phi) return false;
+    if (!poisson_1d_ok(s.g, tx, tt) || !(tx.tw || tx.twm) || !s.Phi) return false;
     uintptr_t any = (uintptr_t)s.F | (uintptr_t)s.Mx | (uintptr_t)s.My | (uintptr_t)s.Mc | (uintptr_t)s.R |
                     (uintptr_t)s.Phi;
     for (int q = 0; q < 4; ++q) any |= (uintptr_t)s.b[q] | (uintptr_t)s.bb[q] | (uintptr_t)s.A[q];
+    // A long problem is many steps for one block, which the three launches of an
+    // iteration spread over the chip: while few problems leave it idle they are faster.
+    // Plain iterations, us, whole and separate: 360 x 32 alone 33.5 and 24.4 (in a
+    // batch's graph 38.9 and 33.2), 24 of them 33.9 and 29.5 (39.2 and 38.8), 32 of them
+    // 33.9 and 31.6 (39.4 and 41.9); 256 x 32 alone 23.6 and 20.4 (27.3 and 27.3), 8 of them
+    // 23.8 and 20.5 (27.6 and 27.1), 12 of them 23.8 and 21.8 (27.6 and 28.6).  360 x 16
+    // alone 20 and 23 (whole iterations from one problem on).  In a batch (frz_run)
+    // 256 x 32 stays whole: beside other groups its launches cost more (8 mixed
+    // problems 49 us an iteration, 52 with them), 360 x 32's less (64 of them 88 and 79).
+    const int nodes = s.g.X * s.g.P;
+    if (s.g.B <= (nodes > 8192 ? 24 : nodes == 8192 && !s.frz_run ? 8 : 0)) return false;
     return any % 16 == 0;          // 16-byte accesses
 }
 
