@@ -214,7 +214,11 @@ int ot_dyn_residuals(ot_dyn_plan* p, float* F, float* Mx, float* My, float* Mc,
 #define OT_PHASE_COUNT    6
 
 /* Enable event timing for the phases in bit mask `mask` (0 disables) and
- * reset the accumulators. */
+ * reset the accumulators.  A plan launches every phase by itself while any is
+ * timed; problems with one spatial axis that otherwise run several whole
+ * iterations in one launch (Y = C = 1 with a fast transform, OT_REFINE_CARRY; the
+ * same results bit for bit) then go phase by phase, and what is timed is those
+ * launches, not the untimed run's. */
 int ot_dyn_profile(ot_dyn_plan* p, int mask);
 
 /* The dual iterate b of Algorithm 1 (Steps 2-4), copied to or from b
@@ -319,11 +323,12 @@ int ot_dyn_batch_get_dual(ot_dyn_batch* bt, float* Bd);
 int ot_dyn_batch_set_dual(ot_dyn_batch* bt, const float* Bd);
 
 /* Selected launch shape of the group holding problem i: row_bx is the block
- * width of the row stencils (64, 128, 256); dense_xy the transform path (0
- * fused three-pass Poisson solve where it applies, else five FFT passes; 1
- * dense x/y contractions; 2 five FFT passes).  For problems with one spatial
- * axis (Y = C = 1, P in {8, 16, 32}) paths 0 and 2 solve the whole Poisson
- * problem in one block per problem (fast transform for X in {64, 128, 256},
+ * width of the row stencils (64, 128, 256); dense_xy the transform path: 0 the
+ * three-pass Poisson solve where one pays (power-of-two sides; the dense one
+ * for other sides or numbers of steps), else a pass per axis; 1 dense x/y
+ * contractions; 2 a pass per axis.  For problems with one spatial axis (Y = C
+ * = 1, P in {8, 16, 32}) paths 0 and 2 solve the whole Poisson problem in one
+ * block per problem (fast transform for X in {64, 100, 128, 180, 256, 360},
  * dense contraction on the matrix cores for other X up to 416). */
 int ot_dyn_batch_tuning(const ot_dyn_batch* bt, int i, int* row_bx, int* dense_xy);
 

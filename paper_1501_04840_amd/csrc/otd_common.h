@@ -260,11 +260,11 @@ void launch_poisson_1d(const Geom& g, float* R, const AxisTab& tx, const AxisTab
                        const double* tt64, const float* frz, hipStream_t st);
 // Whole iterations of such problems with the carried potential and without a
 // residual check, in one launch: the first `refined` of `iters` with the
-// refinement solve.  ok: fast transforms along x, Neumann y, aligned fields.
+// refinement solve.  ok: fast transforms along x, aligned fields, and problems short
+// or many enough for a block each.
 bool iterations_1d_ok(const StepArgs& s, const AxisTab& tx, const AxisTab& tt);
-void launch_iterations_1d(const StepArgs& s, const AxisTab& tx, const AxisTab& ty, const AxisTab& tc,
-                          const AxisTab& tt, const double* tc64, const double* tt64, int iters,
-                          int refined, hipStream_t st);
+void launch_iterations_1d(const StepArgs& s, const AxisTab& tx, const AxisTab& tt, const double* tt64,
+                          int iters, int refined, hipStream_t st);
 
 // Fast power-of-two passes (fastdct.hip); kind 0 DCT-II, 1 DCT-III, 2 Hartley.
 bool fast_len(int L);

@@ -454,7 +454,8 @@ void poisson(ot_dyn_plan* p, float* R) {
 
 // Launch shapes: the row-stencil block width (64, 128 or 256; 0 = default)
 // and the transform path: dense_xy 0 = fused three-pass solve where it
-// applies (else five FFT passes), 1 = dense x/y passes, 2 = five FFT passes.
+// applies, else the dense one where it pays, else five passes; 1 = dense x/y
+// passes, 2 = five passes.
 void apply_tuning(ot_dyn_plan* p, int row_bx, int dense_xy) {
     const Geom& g = p->g;
     if (row_bx <= 0) row_bx = row_block(g.X);
@@ -541,7 +542,7 @@ void iterate_run(ot_dyn_plan* p, const StepArgs& s, int iters) {
             continue;
         }
         const int n = std::min(iters, kRunIters);
-        launch_iterations_1d(s, p->tab[0], p->tab[1], p->tab[2], p->tab[3], p->tc64, p->tt64, n,
+        launch_iterations_1d(s, p->tab[0], p->tab[3], p->tt64, n,
                              std::max(0, std::min(n, p->d.carry_refine - p->it_next)), p->stream);
         p->it_next += n;
         iters -= n;

@@ -1186,16 +1186,16 @@ __global__ void __launch_bounds__(NT) k_iter_1d(TcArgs a, StepArgs s, int iters,
         const bool two = it < refined;         // uniform
         if (two) {
             // r'' = A (a + grad phi_1) - f_b^-, phi_2 from it; phi_1 in R
-    #pragma unroll 1
-        for (int v = tid; v < NV; v += NT) {
+#pragma unroll 1
+            for (int v = tid; v < NV; v += NT) {
                 const int k = v / VL, x = 4 * (v - k * VL);
                 const float* const q = phi + k * PITCH + x;
                 const float o[4] = {q[0], q[1], q[2], q[3]};
                 st4(R + k * L + x, o);
             }
             __syncthreads();
-    #pragma unroll 1
-        for (int v = tid; v < NV; v += NT) {
+#pragma unroll 1
+            for (int v = tid; v < NV; v += NT) {
                 const int k = v / VL, x = 4 * (v - k * VL), i = k * L + x;
                 const bool k0 = k == 0, k1 = k + 1 == P;
                 const int im = k * L + (x == 0 ? L - 1 : x - 1), ip = k * L + (x + 4 == L ? 0 : x + 4);
@@ -1526,12 +1526,10 @@ bool iterations_1d_ok(const StepArgs& s, const AxisTab& tx, const AxisTab& tt) {
     return any % 16 == 0;          // 16-byte accesses
 }
 
-void launch_iterations_1d(const StepArgs& s, const AxisTab& tx, const AxisTab& ty, const AxisTab& tc,
-                          const AxisTab& tt, const double* tc64, const double* tt64, int iters,
-                          int refined, hipStream_t st) {
+void launch_iterations_1d(const StepArgs& s, const AxisTab& tx, const AxisTab& tt, const double* tt64,
+                          int iters, int refined, hipStream_t st) {
     TcArgs a{};
-    a.g = s.g; a.R = s.R; a.tx = tx; a.ty = ty; a.tc = tc; a.tt = tt;
-    a.tc64 = tc64;
+    a.g = s.g; a.R = s.R; a.tx = tx; a.tt = tt;
     a.tt64 = tt64;
     a.twt = tt.tw;
     p1d_run(a, Run1d{&s, iters, refined}, st);
