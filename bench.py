@@ -387,6 +387,7 @@ def hue_render(args):
                    "source_prep_s": source_s},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
+                     "limited_by": "vector instructions and LDS reads of the bin search",
                      "kernel": "k_hue_render", "algorithmic_bytes_per_launch": nbytes,
                      "avg_launch_us": apply_us, "launches": K},
     }

@@ -699,9 +699,12 @@ __device__ __forceinline__ unsigned paint_px(const Px& p, int kout, float fn, fl
 // aligned (and bins_out 16-byte aligned), so a group of four moves as 8 bytes of max
 // and min channels, 16 bytes each of hue, rank and bins, 12 bytes of RGB; the
 // tail group and unaligned images go pixel by pixel.  Bound by its vector
-// instructions, the search's above all.  33 frames of 3840 x 2160, 360 bins: 450 us,
-// a frame alone 24; with the pixels read for each frame, a division, a rounding per
-// channel and search steps at computed addresses 834 and 30.
+// instructions and LDS reads, the search's above all, so its time depends on how far
+// apart neighbouring pixels search: 33 frames of 3840 x 2160, 360 bins, of a smooth
+// image take 400 us along a path of densities and 487 for 33 unrelated ones (a frame
+// alone 24), with random densities 680.  With the pixels read for each frame, a
+// division, a rounding per channel and search steps at computed addresses the
+// unrelated ones took 834 and a frame 30.
 template <bool VEC, int L, int FB>
 __global__ void __launch_bounds__(kThreads) k_hue_render(const unsigned short* __restrict__ hilo,
                                                          const float* __restrict__ hue,

@@ -1111,7 +1111,7 @@ __global__ void __launch_bounds__(NT) k_p1d(TcArgs a) {
 // written.  An iteration then moves 19 words per node instead of 39.
 //
 // A hue batch of 1024 problems (64..360 bins, 16 or 32 steps; ten shapes):
-// 300 iterations of them 63 -> 36 ms, of 64 problems 45 -> 27, of 8 38 -> 15.  What
+// 300 iterations of them 63 -> 36 ms, of 64 problems 39 -> 24, of 8 19 -> 15.  What
 // bounds a block: the latency of its loads and of the transforms between barriers
 // (360 x 32, 100 problems: 36 us an iteration, half of it in the solve); what
 // bounds many: memory (400 of those problems: 75 us, 4.7 TB/s).  Fewer registers by
