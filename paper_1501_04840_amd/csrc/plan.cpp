@@ -171,15 +171,15 @@ int validate(const ot_dyn_desc* d, std::string* why) {
 // (periodic) axis or half-empty tiles lose it once there is enough to do.  The
 // microseconds an iteration gains are estimated as
 //   base + (per node terms below) nodes / 10^6
-// with a row of coefficients per kind of sides and times, least squares over 5500
+// with a row of coefficients per kind of sides and times, least squares over 5800
 // measured shapes: sides 2 to 512, C 1 to 4, P 8 to 64, 10^3 to 2 10^7 nodes in 1 to
 // 1024 problems.  Us per iteration, passes per axis against three: 16 x 16 x 3 x 8
 // 47 and 28 (64 of them 62 and 62), 173 x 131 x 3 x 12 126 and 77, 173 x 64 x 3 x 16 71
 // and 48, 500 x 500 x 3 x 16 6030 and 838, 128 x 128 x 3 x 12 68 and 53; but 200 x 180 x 3
 // x 8, 8 of them, 440 and 478, 128 x 40 x 3 x 16, 4 of them, 84 and 98, 16 x 100 x 3 x 32, 16
-// of them, 143 and 176.  Of the shapes it picks 1% are more than 6% slower for it
-// (worst 23%), of those it leaves 1% would be more than 7% faster; with cuts by side and
-// rows alone 8% were more than 6% slower.
+// of them, 143 and 176, 200 x 32 x 1 x 8, 64 of them, 168 and 257.  Of 7200 shapes those
+// it picks are more than 6% slower for it in 1% (worst 23%), those it leaves would be
+// more than 7% faster in 1%; with cuts by side and rows alone 8% were more than 6% slower.
 // One axis (Y = 1 or X = 1), where the other axis of a tile is padding, by measured
 // cuts: 360 x 1 x 1 x 24, 100 of them, took 72 us per axis and 229 in three passes,
 // 1 x 180 x 3 x 16, 32 of them, 186 and 286; 150 x 1 x 1 x 24, 16 of them, 61 and 46.
@@ -191,15 +191,17 @@ struct DenseGain {
     float base, x32, y32;                   // x32, y32: added for a side of 32 at most
     float node, x, y, inv_x, inv_y;         // per node: 1, X / 100, Y / 100, 10 / X, 10 / Y
     float rows, unfolded, times;            // padded rows of a time group, unfolded sides / 100,
-};                                          // P / 10 (times in registers: C P < 16)
+                                            // P / 10 (times in registers: C P < 16)
+    float fast32;                           // a fast side of 32 (the cheapest transforms)
+};
 constexpr DenseGain kDenseGain[2][2][2] = {     // [times in registers][x fast][y fast]
     {{{36.6f, -5.4f, -6.1f, 34.4f, 2.3f, -0.5f, -20.5f, -7.4f, -20.3f, -2.8f, 2.3f},
       {29.1f, -8.3f, 0.f, 30.7f, 2.6f, -2.1f, -28.2f, -13.1f, -29.3f, 0.f, 6.8f}},
      {{19.6f, 0.f, -5.6f, 11.1f, -1.5f, 3.5f, 21.9f, -3.2f, -14.6f, -1.f, 5.7f},
       {13.1f, 0.f, 0.f, 27.6f, -2.6f, -3.f, -17.5f, -29.9f, -16.4f, -0.9f, 4.f}}},
     {{{21.6f, -5.7f, -4.5f, 9.4f, 4.1f, 3.1f, -21.7f, -8.2f, -9.1f, -3.5f, -8.1f},
-      {16.5f, -10.1f, 0.f, -8.3f, 3.8f, 4.2f, -24.3f, 57.7f, -8.2f, -2.f, -5.9f}},
-     {{6.4f, -0.1f, -6.5f, 5.1f, -3.8f, 5.5f, 4.9f, -0.8f, -9.8f, -3.8f, 0.f}, {}}}};
+      {16.5f, -10.1f, -3.2f, -8.3f, 3.8f, 4.2f, -24.3f, 57.7f, -8.2f, -2.f, -5.9f, -8.3f}},
+     {{6.4f, 1.7f, -6.5f, 5.1f, -3.8f, 5.5f, 4.9f, -0.8f, -9.8f, -3.8f, 0.f, -13.4f}, {}}}};
 
 bool dense3_pays(const Geom& g) {
     if (!dense3_ok(g)) return false;
@@ -224,7 +226,8 @@ bool dense3_pays(const Geom& g) {
     const double base = a.base + (g.X <= 32 ? a.x32 : 0.f) + (g.Y <= 32 ? a.y32 : 0.f);
     const double node = a.node + a.x * X / 100 + a.y * Y / 100 + a.inv_x * 10 / X + a.inv_y * 10 / Y +
                         a.rows * rows + a.unfolded * unfolded +
-                        a.times * (times ? (cp < 16 ? 1.0 : 0.0) : g.P / 10.0);
+                        a.times * (times ? (cp < 16 ? 1.0 : 0.0) : g.P / 10.0) +
+                        ((fx && g.X == 32) || (fy && g.Y == 32) ? a.fast32 : 0.f);
     return base + node * nodes > 0.0;
 }
 

@@ -22,6 +22,9 @@ ROUTES = [
     (16, 100, 3, 32, 16, False),
     (24, 24, 3, 16, 64, False),      # many small ones
     (100, 64, 1, 10, 64, False),     # two fast sides, times without a register transform
+    (200, 32, 1, 8, 64, False),      # a side of 32
+    (32, 70, 1, 16, 64, False),
+    (32, 20, 1, 8, 1, True),
     (16, 16, 3, 8, 1, True),
     (36, 36, 3, 16, 40, True),
     (50, 70, 3, 16, 1, True),
