@@ -180,9 +180,13 @@ int validate(const ot_dyn_desc* d, std::string* why) {
 // of them, 143 and 176, 200 x 32 x 1 x 8, 64 of them, 168 and 257.  Of 7200 shapes those
 // it picks are more than 6% slower for it in 1% (worst 23%), those it leaves would be
 // more than 7% faster in 1%; with cuts by side and rows alone 8% were more than 6% slower.
-// One axis (Y = 1 or X = 1), where the other axis of a tile is padding, by measured
-// cuts: 360 x 1 x 1 x 24, 100 of them, took 72 us per axis and 229 in three passes,
-// 1 x 180 x 3 x 16, 32 of them, 186 and 286; 150 x 1 x 1 x 24, 16 of them, 61 and 46.
+// One axis (Y = 1 or X = 1), where the other axis of a tile is padding, has rows of its
+// own, over 5700 shapes (the gain starts with the colour and time pass it replaces, C P,
+// and an odd length's matrix pass): 1 x 64 x 3 x 40 73 and 26, 32 x 1 x 3 x 40, 16 of them,
+// 118 and 44, 360 x 1 x 4 x 32 134 and 54, 1 x 150 x 1 x 16 41 and 32; but 360 x 1 x 1 x 24, 100
+// of them, 72 and 229, 1 x 300 x 1 x 8, 32 of them, 129 and 169.  1% of the picked are more
+// than 6% slower for it, 1% of the others would be more than 7% faster.  A fast length
+// with times in registers, and a fast y of 512 (1 x 512 x 1 x 48 89 and 132), never.
 // Past the matrix-core passes per axis (500 x 1 x 1 x 12 589 and 50), and for a thin x
 // with a long y (2 x 300 x 3 x 16, 32 of them, 638 and 477), always three passes.
 // Fast sides over 180 with times in registers (512 x 90 x 3 x 32 245 and 309), two fast
@@ -203,6 +207,19 @@ constexpr DenseGain kDenseGain[2][2][2] = {     // [times in registers][x fast][
       {16.5f, -10.1f, -3.2f, -8.3f, 3.8f, 4.2f, -24.3f, 57.7f, -8.2f, -2.f, -5.9f, -8.3f}},
      {{6.4f, 1.7f, -6.5f, 5.1f, -3.8f, 5.5f, 4.9f, -0.8f, -9.8f, -3.8f, 0.f, -13.4f}, {}}}};
 
+struct AxisGain {
+    float base, cp, len;                    // 1, C P / 10, length / 100
+    float node, nlen, inv, rows, unfolded, times;   // per node: as above
+};
+constexpr AxisGain kAxisGain[2][2] = {      // no fast transform; [times in registers][y]
+    {{-4.7f, 6.6f, 9.2f, -74.4f, 5.7f, 7.3f, -3.6f, -0.6f, -26.7f},
+     {-6.7f, 6.9f, 4.2f, -160.3f, 164.4f, 266.3f, -192.6f, 0.f, -5.2f}},
+    {{-2.f, 0.1f, 7.4f, -14.7f, 14.3f, 149.5f, -84.5f, 0.f, -12.f},
+     {-2.8f, -0.1f, 4.7f, -28.8f, 165.4f, 563.2f, -352.9f, 0.f, -11.9f}}};
+constexpr AxisGain kAxisGainFast[2] = {     // a fast one, times without a register one; [y]
+    {-10.2f, 6.4f, -1.3f, -117.7f, -7.5f, -224.8f, 79.8f, -11.f, -26.9f},
+    {-7.9f, 5.7f, 1.5f, 24.8f, -37.9f, 252.1f, -254.7f, 0.f, -15.f}};
+
 bool dense3_pays(const Geom& g) {
     if (!dense3_ok(g)) return false;
     const auto fast = [](int n) { return fast_len(n) || mix_len(n); };
@@ -210,19 +227,26 @@ bool dense3_pays(const Geom& g) {
     const bool times = (g.P == 8 || g.P == 16 || g.P == 32) && (g.C == 1 || g.C == 3);
     const double nodes = 1e-6 * g.B * (double)g.nc;
     if ((!fx && g.X > kMfmaRowsMaxL) || (!fy && g.Y > kMfmaRowsMaxL)) return true;
-    if (!fx && !fy && g.X <= 32 && g.Y >= 256) return true;
-    if (g.X == 1) return g.Y > 1 && !times && nodes <= 0.016;
-    if (g.Y == 1) {
-        if (times && g.C == 1 && g.X <= kP1dDenseMaxL) return false;    // the one-block solve
-        if (fx) return !times && g.C * g.P >= 32 && (g.P > 32 || g.X <= 256) && nodes <= 6e-4 * g.X;
-        return nodes <= (g.X > kP1dDenseMaxL ? 1.5e-3 : times ? 8e-4 : 1.1e-3) * g.X;
+    if (!fx && !fy && g.X > 1 && g.X <= 32 && g.Y >= 256) return true;
+    const int cp = g.C * g.P;
+    const double rows = 16.0 * ((cp + 15) / 16) / cp, X = g.X, Y = g.Y;
+    const double unfolded = ((g.perx ? X : 0.0) + (g.pery ? Y : 0.0)) / 100;
+    if (g.X == 1 || g.Y == 1) {
+        const double n = X * Y;
+        if (g.X == g.Y) return false;
+        if (times && (fx || fy)) return false;
+        // (the one-block solve)
+        if (times && g.Y == 1 && g.C == 1 && g.X <= kP1dDenseMaxL) return false;
+        if (!fx && g.X > kP1dDenseMaxL) return nodes <= 1.5e-3 * n;
+        if (fy && g.Y > 360) return false;
+        const AxisGain& a = fx || fy ? kAxisGainFast[g.X == 1] : kAxisGain[times][g.X == 1];
+        return a.base + a.cp * cp / 10 + a.len * n / 100 +
+                   nodes * (a.node + a.nlen * n / 100 + a.inv * 10 / std::max(n, 16.0) +
+                            a.rows * rows + a.unfolded * unfolded + a.times * g.P / 10) > 0.0;
     }
     if (fx && fy && (times || g.X + g.Y > 320)) return false;
     if (times && ((fx && g.X > 180) || (fy && g.Y > 180))) return false;
     const DenseGain& a = kDenseGain[times][fx][fy];
-    const int cp = g.C * g.P;
-    const double rows = 16.0 * ((cp + 15) / 16) / cp, X = g.X, Y = g.Y;
-    const double unfolded = ((g.perx ? X : 0.0) + (g.pery ? Y : 0.0)) / 100;
     const double base = a.base + (g.X <= 32 ? a.x32 : 0.f) + (g.Y <= 32 ? a.y32 : 0.f);
     const double node = a.node + a.x * X / 100 + a.y * Y / 100 + a.inv_x * 10 / X + a.inv_y * 10 / Y +
                         a.rows * rows + a.unfolded * unfolded +

@@ -18,6 +18,15 @@ ROUTES = [
     (1, 180, 3, 16, 32, False),      # one axis, fast
     (1, 180, 1, 12, 32, False),
     (1, 60, 1, 12, 4, True),         # one axis, few nodes
+    (32, 1, 3, 40, 16, True),        # many colours and times
+    (32, 1, 1, 12, 256, False),
+    (1, 64, 3, 40, 1, True),
+    (1, 512, 1, 48, 1, False),       # a long fast y
+    (150, 1, 3, 16, 1, True),        # times in registers, an odd length
+    (1, 150, 1, 16, 1, True),
+    (1, 300, 1, 8, 32, False),
+    (1, 12, 3, 16, 64, False),
+    (1, 64, 3, 16, 1, False),
     (180, 40, 3, 32, 4, False),      # one fast side
     (16, 100, 3, 32, 16, False),
     (24, 24, 3, 16, 64, False),      # many small ones
