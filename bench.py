@@ -59,14 +59,14 @@ def nt_store(N):
     return 4 * N >= 16 << 20
 
 
-def kernel_name(phase, mode, C, X=0, xfold=False, xkind=0, fused=False, nt=False):
+def kernel_name(phase, mode, C, X=0, xfold=False, xkind=0, fused=False, nt=False, dense=False):
     """Full name of the kernel a steady-state iteration launches for `phase`
     (row stencils and power-of-two transforms).  With xfold the divergence
     kernel also does the forward x transform (DCT-II, xkind 0, or Hartley, 2)
     of its rows of length X; with fused the Poisson solve is the three-pass
     one (x pass into a transposed scratch, the y and time pass, the inverse x
-    pass with the colour transform); nt: the stencil kernels' non-temporal
-    variant (nt_store).  Rows of 128 or 256 nodes take the vector stencil
+    pass with the colour transform), with dense that of the matrix products;
+    nt: the stencil kernels' non-temporal variant (nt_store).  Rows of 128 or 256 nodes take the vector stencil
     kernels (one wavefront per row, X / 64 nodes per lane), the divergence
     without the folded x transform."""
     f = "true" if nt else "false"
@@ -83,6 +83,8 @@ def kernel_name(phase, mode, C, X=0, xfold=False, xkind=0, fused=False, nt=False
         return f"k_update_rows<0, {nphi}, {C}, {f}>"
     if phase == "refine":
         return f"k_div_vec<1, {C}, {f}, {X // 64}>" if vec and not xfold else f"k_div_rows<1, {C}>"
+    if fused and dense:
+        return {"xform_x": "k_dx", "tc": "k_dyt"}[phase]
     if fused:
         return {"xform_x": "k_xf_tr + k_xi_tr", "tc": "k_yt"}[phase]
     return {"xform_x": "k_rows_fft", "xform_y": "k_cols_fft", "tc": "k_tc_reg"}[phase]
@@ -515,6 +517,9 @@ def main():
     # kernel; no y pass: the three-pass solve (y and time in one pass)
     xfold = phases["xform_x"][1] == n_split
     fused = Y > 1 and phases["xform_y"][1] == 0
+    # that of the register transforms takes power-of-two sides and times only
+    pow2 = (32, 64, 128, 256)
+    dense = not (X in pow2 and Y in pow2 and P in (8, 16, 32) and C in (1, 3))
     for name, (ms, n) in phases.items():
         if n == 0:
             continue
@@ -522,7 +527,8 @@ def main():
         mw = METHOD_WORDS[name]
         iter_words += kw * n / n_split
         split[name] = {"ms_per_iter": ms / n_split, "launches": n, "avg_launch_us": 1e3 * ms / n,
-                       "kernel": kernel_name(name, mode, C, X, xfold, fused=fused, nt=nt_store(N)),
+                       "kernel": kernel_name(name, mode, C, X, xfold, fused=fused, nt=nt_store(N),
+                                             dense=dense),
                        "method_words_per_launch": mw, "kernel_words_per_launch": kw,
                        "algorithmic_GBs": mw * 4.0 * N * n / (ms * 1e-3) / 1e9,
                        "kernel_GBs": kw * 4.0 * N * n / (ms * 1e-3) / 1e9}
