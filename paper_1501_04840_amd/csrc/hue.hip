@@ -781,23 +781,24 @@ __global__ void __launch_bounds__(kThreads) k_hue_render(const unsigned short* _
 }
 
 // Launch for counts padded to 2^L, one frame per block or four.  Four read each
-// pixel once for all, but are four serial searches of a block: they pay once their
-// blocks still fill the chip (seven per compute unit, pixel by pixel five), and for
-// 1024 counts, where the searches hide more of the reads, only for four times that.
-// Us, one and four: 64 x 64, 360 bins, 5 frames 38 and 43; 640 x 480 x 33 frames (2700
-// blocks of four) 57 and 60, at 64 bins 36 and 32; 1920 x 1080 x 4 (2025) 55 and 55, at
-// 64 bins 35 and 30; 641 x 479 x 17 (1500) 56 and 53; 3840 x 2160 x 33 526 and 434; 1024
-// bins: 1280 x 720 x 17 (4500) 135 and 142, 1920 x 1080 x 33 (18225) 253 and 240.  Two
-// frames per block of 2048 counts gained nothing.
+// pixel once for all, but are four serial searches of a block: they pay once the
+// frames' blocks still fill the chip in fours (28 a compute unit, pixel by pixel 14),
+// and for 1024 counts, where the searches hide more of the reads, only for four times
+// that.  Us, one and four: 64 x 64, 360 bins, 5 frames 38 and 43; 640 x 480 x 33 frames
+// (39 blocks a unit) 57 and 60, at 64 bins 36 and 32; 1920 x 1080 x 4 (32) 55 and 55, at
+// 64 bins 35 and 30; 641 x 479, 9 frames (11) 46 and 49, 17 (20) 56 and 53; 303 x 1605 x 8,
+// 300 bins (15) 49 and 47; 3840 x 2160 x 33 526 and 434; 1024 bins: 1280 x 720 x 17 (60) 135
+// and 142, 1920 x 1080 x 33 (261) 253 and 240, 1501 x 1001 x 17 (97) 187 and 182, 661 bins
+// 147 and 141.  Two frames per block of 2048 counts gained nothing.
 template <int L>
 void render_launch(bool vec, unsigned blocks, hipStream_t st, const unsigned short* hilo,
                    const float* hue, const unsigned* rank, const int* cum, const long long* shift, int F,
                    int n, long long N, unsigned char* out, int* bins_out) {
     constexpr int FB = L <= 10 ? 4 : 1;
-    const long long enough = 256 * (L == 10 ? 32 : vec ? 7 : 5);
+    const long long enough = 256 * (vec ? 28 : 14) * (L == 10 ? 4 : 1);
     const dim3 block(kThreads);
     const int groups = (F + FB - 1) / FB;
-    if (F == 1 || FB == 1 || (long long)blocks * groups < enough) {
+    if (F == 1 || FB == 1 || (long long)blocks * F < enough) {
         const dim3 grid(blocks, (unsigned)F);
         if (vec) hipLaunchKernelGGL((k_hue_render<true, L, 1>), grid, block, 0, st, hilo, hue, rank,
                                     cum, shift, F, n, N, out, bins_out);

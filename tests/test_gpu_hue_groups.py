@@ -11,8 +11,10 @@ from test_gpu_hue import othue  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-# 2 blocks a frame: four frames per block from 1792 (512 bins and fewer) and 8192 (1024) blocks
-@pytest.mark.parametrize("n,F,npix", [(12, 3585, 2000), (300, 3583, 2000), (512, 3590, 2003), (600, 16385, 1100)])
+# 2 blocks a frame: four frames per block from 7168 blocks in all (512 bins and fewer) and 28672
+# (1024), pixel by pixel from half of that
+@pytest.mark.parametrize("n,F,npix", [(12, 3585, 2000), (300, 3587, 2000), (512, 3590, 2003), (600, 16385, 1100),
+                                      (700, 7171, 1101)])
 def test_many_frames_equal_few(othue, n, F, npix):  # noqa: F811
     import torch
     print(f"hue groups n={n} F={F} npix={npix}", flush=True)
@@ -23,9 +25,9 @@ def test_many_frames_equal_few(othue, n, F, npix):  # noqa: F811
     r = othue.HueRenderer(npix, n, max_frames=F)
     r.set_source(torch.from_numpy(img.reshape(-1)).cuda())
     out, bins = r.render_frames(targets, with_bins=True)
-    for a in range(0, F, 3000):
-        o, b = r.render_frames(targets[a:a + 3000].contiguous(), with_bins=True)
-        assert torch.equal(o, out[a:a + 3000]) and torch.equal(b, bins[a:a + 3000]), a
+    for a in range(0, F, 1500):
+        o, b = r.render_frames(targets[a:a + 1500].contiguous(), with_bins=True)
+        assert torch.equal(o, out[a:a + 1500]) and torch.equal(b, bins[a:a + 1500]), a
     src = ref.Source(img, n)
     for f in (0, F // 2, F - 1):
         rgb_ref, k_ref, _, _ = src.render(targets[f].cpu().numpy())
